@@ -1127,7 +1127,8 @@ __global__ void cast_kernel(int64_t n, const float *__restrict__ x, float *__res
 // bf16 path stages them (byte 4 * (ka % 32) + ka / 32 of row kb), with 2-byte entries hl_rows the
 // entries split into bf16 halves for the hi/lo path.  Every workgroup ORs the whole table for eb
 // (a few tens of KiB, read from L2 after the first) and writes the rows kb of its share;
-// workgroup 0 also writes flags[0] = eb and the zero rows.
+// workgroup 0 also writes flags[0] = eb and the zero rows.  Workgroup b writes flags[kMissFlag + b],
+// the kinds of table that its share of the entries rules out (table_misses); path_flags_kernel ORs them.
 struct TablePrep {
     const uint32_t *lut;
     int m;
@@ -1150,6 +1151,19 @@ __device__ __forceinline__ uint32_t block_or(uint32_t v, uint32_t *s4)
     return s4[0] | s4[1] | s4[2] | s4[3];
 }
 
+// Whether entry i = (ka << m) + kb is not the additive table's, (ka + kb) << (23 - m) (kMissAdd), or
+// not the exact product's of 1.ka and 1.kb (kMissExact), for 3 <= m <= 7 (the matrix-core bodies'
+// kinds kMmaAdd and kMmaExact; Mitchell's multiplier and the exact truncated product).
+constexpr uint32_t kMissAdd = 0x80000000u, kMissExact = 0x40000000u;
+constexpr int kMissFlag = 16;  // of the flags' 64 words, one per table workgroup (table_jobs) from here
+__device__ __forceinline__ uint32_t table_misses(uint32_t entry, int i, int m)
+{
+    const uint32_t n = 1u << m, ka = uint32_t(i) >> m, kb = uint32_t(i) & (n - 1u), e = entry & 0x00FFFFFFu;
+    const uint32_t v = (n + ka) * (n + kb);  // the exact product times n^2, in [n^2, 4 n^2)
+    const uint32_t exact = v >= 2u * n * n ? (1u << 23) + ((v - 2u * n * n) << (22 - 2 * m)) : (v - n * n) << (23 - 2 * m);
+    return (e != (ka + kb) << (23 - m) ? kMissAdd : 0u) | (e != exact ? kMissExact : 0u);
+}
+
 __device__ __forceinline__ void prep_table_body(const TablePrep &t, int bid, int nblk)
 {
     __shared__ uint32_t s_low[4];
@@ -1167,10 +1181,15 @@ __device__ __forceinline__ void prep_table_body(const TablePrep &t, int bid, int
 #pragma unroll 4
         for (int i = threadIdx.x; i < total; i += 256) low |= lut[i];
     }
-    const uint32_t lb = block_or(low & 0xFFFFu, s_low);
-    const int eb = lb == 0u ? 1 : ((lb & 0xFFu) == 0u ? 2 : 4);
+    // the table's kind: each workgroup checks its share of the entries
+    low &= 0xFFFFu;
+    if (t.m >= 3)
+        for (int i = bid * 256 + int(threadIdx.x); i < total; i += nblk * 256) low |= table_misses(lut[i], i, t.m);
+    const uint32_t lb = block_or(low, s_low);
+    const int eb = (lb & 0xFFFFu) == 0u ? 1 : ((lb & 0xFFu) == 0u ? 2 : 4);
     const bool lead = bid == 0;
     if (lead && threadIdx.x == 0) t.flags[0] = eb;
+    if (threadIdx.x == 0) t.flags[kMissFlag + bid] = int(t.m < 3 ? kMissAdd | kMissExact : lb & (kMissAdd | kMissExact));
     const int per = (n + nblk - 1) / nblk, kb0 = bid * per, nk = max(0, min(n, kb0 + per) - kb0);
     unsigned char *__restrict__ dst = t.rows;
     // rows: thread -> (kb, group of 4 entries), consecutive threads along kb
@@ -1303,7 +1322,7 @@ __global__ __launch_bounds__(256) void prep_rows_wide_kernel(const uint32_t *__r
             const uint32_t a_hs = max(max(s_ahs[0], s_ahs[1]), max(s_ahs[2], s_ahs[3]));
             const uint32_t b_hs = max(max(s_bhs[0], s_bhs[1]), max(s_bhs[2], s_bhs[3]));
             int path, rounded;
-            decide_paths(eb, 0u, a_hs, 0u, b_hs, have, narrow, path, rounded);
+            decide_paths(eb, 0, 0u, a_hs, 0u, b_hs, have, narrow, path, rounded);
             flags[0] = eb;
             flags[1] = 0;
             flags[2] = rounded;
@@ -1332,10 +1351,10 @@ __global__ __launch_bounds__(256) void prep_rows_wide_kernel(const uint32_t *__r
 
 // The path flags of a call on rows of 128 entries whose table kernel reads them (kTabApprox):
 // flags[1] and flags[2] (decide_paths) from the decode statistics, once the pre-pass has written
-// the entry width flags[0].  One workgroup.
+// the entry width flags[0] and its n_tab table workgroups' words.  One workgroup.
 __global__ __launch_bounds__(1024) void path_flags_kernel(const uint32_t *__restrict__ stats_a, int n_a,
                                                           const uint32_t *__restrict__ stats_b, int n_b, int narrow,
-                                                          int *__restrict__ flags)
+                                                          int n_tab, int *__restrict__ flags)
 {
     __shared__ uint32_t red[16][4];
     uint32_t alo = 255u, ahs = 0u, blo = 255u, bhs = 0u;
@@ -1361,8 +1380,11 @@ __global__ __launch_bounds__(1024) void path_flags_kernel(const uint32_t *__rest
             b_lo = min(b_lo, red[w][2]);
             b_hs = max(b_hs, red[w][3]);
         }
+        uint32_t miss = 0u;
+        for (int i = 0; i < n_tab; ++i) miss |= uint32_t(flags[kMissFlag + i]);
+        const int kind = (miss & kMissAdd) == 0u ? kMmaAdd : ((miss & kMissExact) == 0u ? kMmaExact : 0);
         int path, rounded;
-        decide_paths(flags[0], a_lo, a_hs, b_lo, b_hs, true, narrow, path, rounded);
+        decide_paths(flags[0], kind, a_lo, a_hs, b_lo, b_hs, true, narrow, path, rounded);
         flags[1] = path;
         flags[2] = rounded;
     }
@@ -1575,15 +1597,16 @@ int run_prepass(const PrepJobs &j, const A &a, size_t lds, int var, int narrow, 
                            j.t.part, j.n_tab, j.stats_a, j.n_a, j.stats_b, j.n_b, narrow, j.t.rows, j.t.flags);
     } else if (var == kTabApprox) {
         hipLaunchKernelGGL(path_flags_kernel, dim3(1), dim3(1024), 0, st, j.stats_a, j.n_a, j.stats_b, j.n_b, narrow,
-                           j.t.flags);
+                           j.n_tab, j.t.flags);
     }
     return launch_status();
 }
 
 // The pointers of a launch's arguments (the rest is the plan's geometry, g).
-TabArgs tab_args(TabArgs g, const Plan &p, char *ws, const uint32_t *A, const uint32_t *Bd, float *out)
+TabArgs tab_args(TabArgs g, const Plan &p, int mb, char *ws, const uint32_t *A, const uint32_t *Bd, float *out)
 {
     TabArgs a = g;
+    a.m = mb;
     a.A = A;
     a.Bd = Bd;
     a.out = out;
@@ -1848,7 +1871,7 @@ int gemm_run(const Mode &md, int trans_a, int trans_b, int64_t m, int64_t n, int
     if (run_prepass(j, da, 0, var, narrow_of(md), st) != AMSIM_OK) return AMSIM_ERR_HIP;
     int rc;
     {
-        TabArgs a = tab_args(gemm_geom(p, m, n, k, ldc), p, ws, Ad, Bd, out);
+        TabArgs a = tab_args(gemm_geom(p, m, n, k, ldc), p, mb, ws, Ad, Bd, out);
         set_stats(a, j, md);
         set_format_scales(a, md);
         const dim3 grid = dim3_of(gemm_grid(p));
@@ -1961,7 +1984,7 @@ int fwd_core(const Mode &md, const amsim_conv2d *desc, const float *x, const flo
         rc = run_prepass(j, da, lds, var, narrow_of(md), st);
     }
     if (rc != AMSIM_OK) return AMSIM_ERR_HIP;
-    TabArgs a = tab_args(fwd_geom(p, s), p, ws, Xd, Wd, out);
+    TabArgs a = tab_args(fwd_geom(p, s), p, mb, ws, Xd, Wd, out);
     set_stats(a, j, md);
     set_format_scales(a, md);
     const dim3 grid = dim3_of(fwd_grid(p, s));
@@ -2009,7 +2032,7 @@ int bwd_data_run(const Mode &md, const amsim_conv2d *desc, const Plan &p, const 
     j.n_b = decode_grid(int64_t(s.kh) * s.kw * s.co * p.b_ld);
     const int var = tab_variant(md, p, conv_macs(s));
     if (run_prepass(j, da, lds, var, narrow_of(md), st) != AMSIM_OK) return AMSIM_ERR_HIP;
-    TabArgs a = tab_args(bwd_data_geom(p, s), p, ws, Dyd, Wtd, out);
+    TabArgs a = tab_args(bwd_data_geom(p, s), p, mb, ws, Dyd, Wtd, out);
     set_stats(a, j, md);
     set_format_scales(a, md);
     const dim3 grid = dim3_of(bwd_data_grid(p, s));
@@ -2102,7 +2125,7 @@ int conv_bwd_weight_run(const Mode &md, const amsim_conv2d *desc, const float *x
     float *out = p.splits > 1 ? reinterpret_cast<float *>(ws + p.off_part) : dw;
     {
         TimedLaunch tl(md.native ? AMSIM_KERNEL_CONV_BWD_WEIGHT_NATIVE : AMSIM_KERNEL_CONV_BWD_WEIGHT, st);
-        TabArgs a = tab_args(bwd_weight_geom(p, s), p, ws, Xd, Dyd, out);
+        TabArgs a = tab_args(bwd_weight_geom(p, s), p, mb, ws, Xd, Dyd, out);
         set_stats(a, j, md);
         set_format_scales(a, md);
         const dim3 grid = dim3_of(bwd_weight_grid(p, s));

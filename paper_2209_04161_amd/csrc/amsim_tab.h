@@ -8,8 +8,9 @@
 // the column's second-operand mantissa selects (128 entries for M <= 7, 2^M for M = 8..11);
 // lanes gather from it with their first-operand mantissas.  For 1-byte tables and operands
 // whose exponents keep every product normal, the bf16 pair path folds the second operand into
-// the staged entries and adds two steps' products with one dot instruction.  Products are
-// never fed to MFMA: they are not IEEE.
+// the staged entries and adds two steps' products with one dot instruction.  Tables that are an
+// integer sum of the mantissas, or the exact product, are computed without a table and added on the
+// matrix cores (large calls).
 #pragma once
 
 #include <type_traits>
@@ -60,9 +61,10 @@ struct TabArgs {
     const unsigned char *rows;      // transposed table rows (exact path)
     const unsigned char *dot_rows;  // the same 1-byte rows in bf16-path staging order
     const unsigned char *hl_rows;   // 2-byte tables: entries split into bf16 halves (hi/lo path)
-    const int *eb;                  // [0] entry width, [1] 1 (2) when the bf16 (hi/lo) path may run,
-                                    // [2] 1 when the exact path rounds each product before adding it,
-                                    // [3] (rows of 256 entries or more) 1 when the table is sum-indexed
+    const int *eb;                  // [0] entry width, [1] 1 (2) when the bf16 (hi/lo) path may run, 3 or 4
+                                    // for the matrix-core bodies, [2] 1 when the exact path rounds each
+                                    // product before adding it, [3] (rows of 256 entries or more) 1 when
+                                    // the table is sum-indexed
     const uint32_t *stats_a, *stats_b;  // kTabApproxSelf: the decode passes' exponent statistics
     int n_a, n_b;                       // (null: none), words of each operand, and whether the
     int narrow;                         // operands are cast to fewer exponent bits than FP32's
@@ -70,6 +72,7 @@ struct TabArgs {
     float su, sd;        // ... and each product by su, then added times sd (1, 1, 1 for FP32 operands)
     int R, N;            // result rows and columns
     int splits;          // reduction splits: tile z = (phase *) splits + split
+    int m;               // mantissa bits of the table index
     int chunk;           // steps per reduction chunk (8)
     int chunks_per_split;  // reduction chunks per split
     int64_t out_elems;   // elements of one split's partial result (splits > 1)
@@ -81,6 +84,7 @@ struct TabArgs {
     int csplit;          // FWD / BWD_DATA: channel chunks; taps run chunk-major (csplit divides s.ci / s.co
                          // into multiples of 8)
     int OHp, OWp, pad_oh, pad_ow;  // zero-padded dy (BWD_DATA)
+    int gx, gy, gz;      // the launch's tiles: row blocks, column blocks, phases x splits
     int tx, ty, tz;      // this workgroup's tile (row block, column block, phase/split); set on entry
 };
 
@@ -89,22 +93,24 @@ struct TabArgs {
 // (phases differ in work, so each XCD gets all of them), then column blocks, row blocks, splits --
 // so that the workgroups an XCD runs together share first-operand rows and second-operand cache
 // lines in its L2.  Grids whose size is not a multiple of 8 keep the hardware order.
-__device__ __forceinline__ void tab_tile_id(int splits, int &tx, int &ty, int &tz)
+__device__ __forceinline__ bool tab_tile_id(TabArgs &a)
 {
-    const uint32_t gx = gridDim.x, gy = gridDim.y, gz = gridDim.z, n = gx * gy * gz;
-    const uint32_t id = blockIdx.x + gx * (blockIdx.y + gy * blockIdx.z);
+    const uint32_t gx = uint32_t(a.gx), gy = uint32_t(a.gy), gz = uint32_t(a.gz), n = gx * gy * gz;
+    const uint32_t id = blockIdx.x;
+    if (id >= n) return false;
     if (n % 8u != 0u) {
-        tx = int(blockIdx.x);
-        ty = int(blockIdx.y);
-        tz = int(blockIdx.z);
-        return;
+        a.tx = int(id % gx);
+        a.ty = int((id / gx) % gy);
+        a.tz = int(id / (gx * gy));
+        return true;
     }
     const uint32_t lid = (id % 8u) * (n / 8u) + id / 8u;
-    const uint32_t phases = gz / uint32_t(splits);
+    const uint32_t phases = gz / uint32_t(a.splits);
     const uint32_t ph = lid % phases, rest = lid / phases;
-    ty = int(rest % gy);
-    tx = int((rest / gy) % gx);
-    tz = int(ph * uint32_t(splits) + rest / (gx * gy));
+    a.ty = int(rest % gy);
+    a.tx = int((rest / gy) % gx);
+    a.tz = int(ph * uint32_t(a.splits) + rest / (gx * gy));
+    return true;
 }
 
 struct TabTap {
@@ -961,6 +967,24 @@ __device__ __forceinline__ uint32_t add_u16x2(uint32_t x, uint32_t y)
     return __builtin_bit_cast(uint32_t, __builtin_bit_cast(u16x2_t, x) + __builtin_bit_cast(u16x2_t, y));
 }
 
+// Saturating unsigned difference of both halves.
+__device__ __forceinline__ uint32_t sub_sat_u16x2(uint32_t x, uint32_t y)
+{
+    return __builtin_bit_cast(uint32_t, __builtin_elementwise_sub_sat(__builtin_bit_cast(u16x2_t, x),
+                                                                      __builtin_bit_cast(u16x2_t, y)));
+}
+
+__device__ __forceinline__ uint32_t min_u16x2(uint32_t x, uint32_t y)
+{
+    return __builtin_bit_cast(uint32_t, __builtin_elementwise_min(__builtin_bit_cast(u16x2_t, x),
+                                                                  __builtin_bit_cast(u16x2_t, y)));
+}
+
+__device__ __forceinline__ uint32_t mul_u16x2(uint32_t x, uint32_t y)
+{
+    return __builtin_bit_cast(uint32_t, (u16x2_t)(__builtin_bit_cast(u16x2_t, x) * __builtin_bit_cast(u16x2_t, y)));
+}
+
 // Staging of one slab: thread -> step slot (tid / 32) and entry group g (tid % 32), which builds
 // the entries ka = g, g + 32, g + 64, g + 96.  Fetch, in two parts: the slot's DC second-operand
 // words, then, per column, the 4 bytes of its table row that hold those entries.
@@ -1312,6 +1336,304 @@ __device__ __forceinline__ void tab_body_dot(const TabArgs &a)
     dot_finish<OP, TM, TN>(a, acc, av, row0, col0, R, q0, cpt, p_end, ch);
 }
 
+// ------------------------------------------------- matrix-core bodies (M = 3..7)
+// Two kinds of table need no table lookup inside the bf16 path's operand window (decide_paths), and
+// let the matrix cores add the products.  The table preparation checks every entry for both
+// (flags[3]).  The first operand a and the second operand b are bf16 bit patterns here, cut to M
+// mantissa bits.
+//
+// kMmaAdd, an additive table (Mitchell's): entry (ka, kb) = (ka + kb) << (23 - M), the carry falling
+// into its bit 23.  The factor times the first operand, t = v * pa, is then an integer sum of bit
+// patterns, bits(t) = bits(a) + kb.  Every (row, step, column) has its own t, one packed 16-bit
+// operation per two of them, and t goes through the matrix core as the left operand: for column j,
+// t of 16 rows x 32 steps times a right operand whose column j holds pb of the 32 steps and whose
+// other 15 columns are zero, which adds sum over the steps of t * pb to column j of the 16 x 16
+// result.  A zero first operand has to give t = 0 whatever kb is: bits(t) = (bits(a) + 128) -
+// (128 - kb) as a saturating unsigned subtraction, where a zero's bits(a) + 128 is stored as 0; the
+// sign rides on top, and bits(a) + 128 and t stay finite (the window keeps a's exponent field below
+// 254).  A zero second operand has pb = 0.
+//
+// kMmaExact, the exact product of the cut operands: t * pb summed over 32 steps for all 16 columns
+// is one matrix instruction.
+//
+// Products are exact in FP32 either way and are added by the matrix core in FP32.
+//
+// What bounds it: kMmaAdd issues, per 512 products, four packed subtractions and one matrix
+// instruction that occupies the SIMD for about three more issue slots -- a loop of just these reaches
+// 45 T products/s, the pair path's VALU limit is 34 T -- with two 16-byte LDS reads per 4096 products
+// instead of one gather per eight.  Measured on MI355X: the GEMM 4096^3 2.98 -> 1.95 ms (35 T products/s),
+// the three ResNet 3x3 passes 857 -> 677 us with their pre-passes.  Two columns per dot instruction (one
+// packed subtraction, one dot per two products) were tried first: 36 T at best in a loop, 28 T in the
+// GEMM.  kMmaExact is bound by the records' loads: the 1x1 1024 -> 256 layer's kernels 203 -> 23 us.
+constexpr int kMmaAdd = 1, kMmaExact = 2;
+typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
+typedef float f32x4_t __attribute__((ext_vector_type(4)));
+
+__device__ __forceinline__ f32x4_t mma_16x16x32(u32x4 x, u32x4 y, f32x4_t c)
+{
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, x), __builtin_bit_cast(bf16x8_t, y), c,
+                                                   0, 0, 0);
+}
+
+// A workgroup of NW waves: 32 NW rows x 16 WC columns, a wave 32 WC rows (2 WC blocks of 16) x 16
+// columns.  WC = 4 where there are more than 32 columns, so that a staged row serves 64 columns, else 2.
+struct MmaTiles {
+    int wc, nrow, ncol;
+};
+__host__ __device__ __forceinline__ MmaTiles mma_tiles(int rows, int cols, int nw)
+{
+    MmaTiles t;
+    t.wc = cols > 32 ? 4 : 2;
+    t.nrow = (rows + 32 * nw - 1) / (32 * nw);
+    t.ncol = (cols + 16 * t.wc - 1) / (16 * t.wc);
+    return t;
+}
+
+// LDS: two slabs of 32 steps (4 reduction chunks), each [row][4 x 16 bytes] of the first operand, the
+// 16-byte pieces of a row permuted by its bits 2..3 so that 16 rows' pieces cover the banks, and
+// [2][4][column][16 bytes] of the second (128 - kb or, kMmaExact, b; and pb), and 256 bytes of
+// zeros, which the lanes of the other columns read in place of pb.
+constexpr int mma_a_bytes(int nw) { return 32 * nw * 64; }
+constexpr int mma_b_bytes(int wc) { return 2 * 4 * 16 * wc * 16; }
+constexpr size_t mma_lds_bytes(int nw) { return 2 * size_t(mma_a_bytes(nw) + mma_b_bytes(4)) + 256; }
+
+template <int OP, int NW, int WC, int KIND>
+__device__ __forceinline__ void tab_body_mma(const TabArgs &a0, const MmaTiles &mt)
+{
+    constexpr int NT = 64 * NW;
+    constexpr int RT = 2 * WC, WR = NW / WC;
+    constexpr int ROWS = 32 * NW, COLS = 16 * WC;
+    constexpr int ABYTES = mma_a_bytes(NW), BHALF = mma_b_bytes(WC) / 2, BUF = ABYTES + mma_b_bytes(WC);
+    constexpr int BU = COLS * 16;               // staged step pairs of the second operand per slab
+    constexpr int BPH = (BU / 2 + NT - 1) / NT;  // of them per thread and half of the slab's columns' work
+    static_assert(WR * WC == NW && NT == 2 * ROWS, "workgroup shape");
+    TabArgs a = a0;
+    // this workgroup's tile: contiguous ranges of tiles per XCD, in tab_tile_id's order
+    const uint32_t tiles = uint32_t(mt.nrow) * uint32_t(mt.ncol) * uint32_t(a.gz);
+    uint32_t id = blockIdx.x;
+    if (gridDim.x % 8u == 0u) {
+        const uint32_t per = (tiles + 7u) / 8u;
+        if (id / 8u >= per) return;
+        id = (id % 8u) * per + id / 8u;
+    }
+    if (id >= tiles) return;
+    const uint32_t phases = uint32_t(a.gz) / uint32_t(a.splits);
+    const uint32_t ph = id % phases, rest = id / phases;
+    const int ty = int(rest % uint32_t(mt.ncol)), rest2 = int(rest / uint32_t(mt.ncol));
+    const int tx = rest2 % mt.nrow;
+    a.tz = int(ph) * a.splits + rest2 / mt.nrow;
+
+    const int R = tab_rows<OP>(a);
+    if (tx * ROWS >= R) return;  // uniform over the workgroup
+    const int lane = threadIdx.x & 63, n = lane & 15, g = lane >> 4;
+    const int wave = wave_id();
+    const int cg = wave % WC, rg = wave / WC;
+    const int roww = tx * ROWS, row0 = roww + rg * (16 * RT);
+    const int colw = ty * COLS, col0 = colw + cg * 16;
+    const bool live = row0 < R && col0 < a.N;   // wave-uniform
+    const int nj = min(16, a.N - col0);         // the wave's columns
+    const int m = a.m;
+
+    const int count = tab_count<OP>(a), ch = a.chunk;  // ch = 8 steps: a quarter of a slab
+    const int cpt = (count + ch - 1) / ch, ppt = (count + 1) / 2;
+    const int q_total = tab_taps<OP>(a) * cpt;
+    const int q0 = tab_split(a) * a.chunks_per_split, q1 = min(q_total, q0 + a.chunks_per_split);
+
+    // staging of the first operand: this thread's row and, of each slab, chunks sc and sc + 2
+    const int srow = int(threadIdx.x) % ROWS, sc = __builtin_amdgcn_readfirstlane(int(threadIdx.x) / ROWS);
+    const __amdgpu_buffer_rsrc_t arec =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t *>(a.A), 0, int(a.a_bytes), 0x00020000);
+    // rows past the end read record 0's run
+    const uint32_t aoff = uint32_t(roww + srow < R ? tab_row_rec<OP>(a, roww + srow) : 0) * kPairRecordBytes;
+    const uint32_t a_dst = uint32_t(srow) * 64u, a_swz = uint32_t(srow >> 2) & 3u;
+    u32x3 sa[4];
+    uint32_t sb[BPH][2];
+    auto chunk_tap = [&](int q, TabTap &tp, int &c0) __attribute__((always_inline)) {
+        const int tap = OP == OP_GEMM ? 0 : q / cpt;
+        tp = tab_tap_raw<OP>(a, tap);
+        c0 = (q - tap * cpt) * ch;
+    };
+    // A slab is staged in two halves, each fetched before half of the previous slab's products and
+    // written after them: chunks sc (half 0) and sc + 2 (half 1) of the thread's row, and half of the
+    // second operand's step pairs.
+    auto fetch = [&](int qs, int half) __attribute__((always_inline)) {
+        {
+            const int q = min(qs + sc + 2 * half, q1 - 1);  // past the end: finite values, against zeros of b
+            TabTap tp;
+            int c0;
+            chunk_tap(q, tp, c0);
+#pragma unroll
+            for (int p = 0; p < 4; ++p) {
+                const uint32_t so = __builtin_amdgcn_readfirstlane(
+                    uint32_t(tp.pbase + min(c0 / 2 + p, ppt - 1) * tp.ustride) * kPairRecordBytes);
+                sa[p] = __builtin_amdgcn_raw_buffer_load_b96(arec, aoff, so, 0);
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < BPH; ++i) {
+            const int u = int(threadIdx.x) + i * NT, col = colw + u % COLS, pr = u / COLS + 8 * half, q = qs + pr / 4;
+            sb[i][0] = sb[i][1] = kZeroRowWord;
+            if (u < BU / 2 && q < q1 && col < a.Np) {
+                TabTap tp;
+                int c0;
+                chunk_tap(q, tp, c0);
+                const int j = c0 + 2 * (pr % 4);
+                if (j < count) sb[i][0] = Bd_word(a, tp.bbase + j, col);
+                if (j + 1 < count) sb[i][1] = Bd_word(a, tp.bbase + j + 1, col);
+            }
+        }
+    };
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    auto commit = [&](int buf, int half) __attribute__((always_inline)) {
+        unsigned char *ab = smem + buf * BUF, *bb = ab + ABYTES;
+        u32x4 v;
+#pragma unroll
+        for (int p = 0; p < 4; ++p) {
+            const u32x3 rec = sa[p];  // index words ka << 4, ka of M bits
+            const uint32_t w = rec.y + (((rec.z << 16) | rec.x) >> (m - 3));
+            v[p] = KIND == kMmaAdd ? mul_u16x2(w + 0x00800080u, min_u16x2(rec.y & 0x7FFF7FFFu, 0x00010001u)) : w;
+        }
+        *reinterpret_cast<u32x4 *>(ab + a_dst + ((uint32_t(sc + 2 * half) ^ a_swz) << 4)) = v;
+#pragma unroll
+        for (int i = 0; i < BPH; ++i) {
+            const int u = int(threadIdx.x) + i * NT, col = u % COLS, pr = u / COLS + 8 * half;
+            if (BU / 2 % NT != 0 && u >= BU / 2) break;
+            uint32_t k[2], h[2];
+#pragma unroll
+            for (int e = 0; e < 2; ++e) {  // a zero's index is the zero row's: no mantissa bits
+                k[e] = (sb[i][e] & 0x3F80u) >> m;
+                h[e] = sb[i][e] >> 16;
+            }
+            unsigned char *dst = bb + ((pr / 4) * COLS + col) * 16 + (pr % 4) * 4;
+            const uint32_t kk = k[0] | (k[1] << 16), hh = h[0] | (h[1] << 16);
+            *reinterpret_cast<uint32_t *>(dst) = KIND == kMmaAdd ? 0x00800080u - kk : hh + kk;
+            if (KIND == kMmaAdd) *reinterpret_cast<uint32_t *>(dst + BHALF) = hh;
+        }
+    };
+
+    f32x4_t acc[RT];
+#pragma unroll
+    for (int r = 0; r < RT; ++r) acc[r] = f32x4_t{-0.0f, -0.0f, -0.0f, -0.0f};
+    // lanes of other columns read zeros: at zoff + BHALF + 0 or 16
+    const uint32_t zoff = 2 * BUF - BHALF;
+    if (threadIdx.x < 64) reinterpret_cast<uint32_t *>(smem + 2 * BUF)[threadIdx.x] = 0u;
+    const uint32_t a_src = uint32_t(rg * (16 * RT) + n) * 64u + ((uint32_t(g) ^ (uint32_t(n >> 2) & 3u)) << 4);
+    const uint32_t b_src = ABYTES + uint32_t(g * COLS + cg * 16) * 16u;
+    int buf = 0;
+    bool have = false;
+    for (int qs = q0;; qs += 4) {  // slab qs is staged while the one before it is computed
+        const bool more = qs < q1;
+        const uint32_t base = uint32_t(buf ^ 1) * BUF;
+        u32x4 af[RT];
+        if (live && have) {
+#pragma unroll
+            for (int r = 0; r < RT; ++r) af[r] = lds_load_b128(base + a_src, r * 1024);
+        }
+#pragma unroll
+        for (int half = 0; half < 2; ++half) {
+            if (more) fetch(qs, half);
+            if (live && have) {
+                if constexpr (KIND == kMmaExact) {
+                    if (half == 0) {
+                        const u32x4 bf = lds_load_b128(base + b_src + uint32_t(n) * 16u, 0);
+#pragma unroll
+                        for (int r = 0; r < RT; ++r) acc[r] = mma_16x16x32(af[r], bf, acc[r]);
+                    }
+                } else {
+                    // columns in pairs, a column's words read while the one before it is computed;
+                    // a last odd column is followed by a column past the end, which is not stored
+                    int j = half == 0 ? 0 : (nj + 2) / 4 * 2;
+                    const int j1 = half == 0 ? (nj + 2) / 4 * 2 : nj;
+                    uint32_t src = base + b_src + uint32_t(j) * 16u;
+                    auto column = [&](u32x4 kc, u32x4 pc) __attribute__((always_inline)) {
+                        u32x4 t;
+#pragma unroll
+                        for (int r = 0; r < RT; ++r) {
+#pragma unroll
+                            for (int e = 0; e < 4; ++e) t[e] = sub_sat_u16x2(af[r][e], kc[e]);
+                            acc[r] = mma_16x16x32(t, pc, acc[r]);
+                        }
+                        asm volatile("" : "+v"(src) : "v"(t));  // later columns' loads stay behind this one
+                    };
+                    u32x4 k0 = lds_load_b128(src, 0), p0 = lds_load_b128(n == j ? src : zoff, BHALF);
+                    for (; j < j1; j += 2) {
+                        const u32x4 k1 = lds_load_b128(src, 16), p1 = lds_load_b128(n == j + 1 ? src : zoff, BHALF + 16);
+                        column(k0, p0);
+                        src += 32u;
+                        k0 = lds_load_b128(src, 0);
+                        p0 = lds_load_b128(n == j + 2 ? src : zoff, BHALF);
+                        column(k1, p1);
+                    }
+                }
+            }
+            if (more) commit(buf, half);
+        }
+        if (!more) break;
+        __syncthreads();
+        buf ^= 1;
+        have = true;
+    }
+    if (!live) return;
+
+    // Signs of exactly-zero sums, as in dot_finish: -0 when every product of the split's range is
+    // -0, else +0.  Lane (n, g) holds rows 16 r + 4 g + i of column n.
+    const int col = col0 + n;
+    const bool colok = col < a.N;
+#pragma unroll
+    for (int h = 0; h < RT; h += 2) {  // two row blocks at a time
+        uint32_t pending = 0u;
+        uint32_t ro[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const int row = row0 + 16 * (h + i / 4) + 4 * g + i % 4;
+            ro[i] = 0u;
+            if (colok && row < R && acc[h + i / 4][i % 4] == 0.0f) pending |= 1u << i;
+        }
+        const uint32_t zero = pending;
+        if (__builtin_amdgcn_ballot_w64(pending != 0u) != 0u) {
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const int row = row0 + 16 * (h + i / 4) + 4 * g + i % 4;
+                if (row < R) ro[i] = uint32_t(tab_row_rec<OP>(a, row)) * kPairRecordBytes;
+            }
+            for (int p = q0 * ch; p < q1 * ch && __builtin_amdgcn_ballot_w64(pending != 0u) != 0u; ++p) {
+                const int tap = p / (cpt * ch), j = p - tap * (cpt * ch);
+                if (j >= count) continue;  // a chunk's padding steps
+                const TabTap tp = tab_tap<OP>(a, tap);
+                const uint32_t so = __builtin_amdgcn_readfirstlane(a_step_offset<OP>(tp, j));
+                const float pb = colok ? head_value(Bd_word(a, tp.bbase + j, col)) : 0.0f;
+#pragma unroll
+                for (int i = 0; i < 8; ++i) {
+                    const u32x2 d = __builtin_amdgcn_raw_buffer_load_b64(arec, ro[i], so + (j & 1) * 4u, 0);
+                    const uint32_t w = __builtin_amdgcn_perm(d.y, d.x, (j & 1) ? 0x03020504u : 0x05040100u);
+                    if (__float_as_uint(head_value(w) * pb) != 0x80000000u) pending &= ~(1u << i);
+                }
+            }
+#pragma unroll
+            for (int i = 0; i < 8; ++i)
+                if ((zero >> i) & 1u) acc[h + i / 4][i % 4] = ((pending >> i) & 1u) ? -0.0f : 0.0f;
+        }
+    }
+    float *out = a.out + int64_t(tab_split(a)) * a.out_elems + col;
+#pragma unroll
+    for (int r = 0; r < RT; ++r)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int row = row0 + 16 * r + 4 * g + i;
+            if (colok && row < R) out[tab_row_out<OP>(a, row)] = acc[r][i];
+        }
+}
+
+template <int OP, int NW, int KIND>
+__device__ __forceinline__ void tab_mma(const TabArgs &a)
+{
+    const MmaTiles mt = mma_tiles(a.R, a.N, NW);
+    if (mt.wc == 4)
+        tab_body_mma<OP, NW, 4, KIND>(a, mt);
+    else
+        tab_body_mma<OP, NW, 2, KIND>(a, mt);
+}
+
 // ------------------------------------------------------- bf16 hi/lo path (2-byte tables)
 // A 2-byte entry's value v has up to 16 significant bits: too many for one bf16, but v is the sum
 // of two bf16 values v_hi (its top 8 bits) and v_lo (the rest; where that is zero, v_hi is
@@ -1544,16 +1866,24 @@ __device__ __forceinline__ int exact_needs_rounded_products(bool have_stats, boo
 //     exponent field Ea + Eb - 127 + carry in [1, 254], and v * pb (Eb + carry) stays below 255;
 //   path 2, the hi/lo path (2-byte entries): also the low halves' products normal -- v_lo >=
 //     2^-15 times pb normal as a bf16 (Eb >= 16) and times pa normal (Ea + Eb - 127 - 15 >= 1);
+//   paths 3 and 4 (2 + kind), the matrix-core bodies (kind: the table's, 0 in a small call, whose
+//     launches take longer than its products: the kernel that decides its path itself leaves them out,
+//     which keeps it small -- with them a 64^3 GEMM's took 9.2 us instead of 6.1):
+//   path 3, in path 1's window, Ea + carry below 255 too: an additive table (kind kMmaAdd);
+//   path 4, in path 1's window: the exact product (kind kMmaExact);
 //   path 0, the exact path, whose product form is `rounded`.
 // have: the decode passes recorded statistics (not for the native multiply).
-__device__ __forceinline__ void decide_paths(int eb, uint32_t a_lo, uint32_t a_hs, uint32_t b_lo, uint32_t b_hs,
+__device__ __forceinline__ void decide_paths(int eb, int kind, uint32_t a_lo, uint32_t a_hs, uint32_t b_lo, uint32_t b_hs,
                                              bool have, int narrow, int &path, int &rounded)
 {
     const uint32_t a_hi = a_hs & 0xFFu, b_hi = b_hs & 0xFFu;
     const bool special = ((a_hs | b_hs) >> 8) != 0u;
     const bool window = have && !special && a_lo + b_lo >= 128u && a_hi + b_hi <= 380u && b_hi <= 253u;
     const bool window_hl = window && b_lo >= 16u && a_lo + b_lo >= 143u;
-    path = narrow ? 0 : ((eb == 1 && window) ? 1 : ((eb == 2 && window_hl) ? 2 : 0));
+    path = (eb == 1 && window) ? 1 : ((eb == 2 && window_hl) ? 2 : 0);
+    if (kind == kMmaAdd && window && a_hi <= 253u) path = 3;
+    if (kind == kMmaExact && window) path = 4;
+    if (narrow) path = 0;
     rounded = exact_needs_rounded_products(have, special, a_hi, b_hi, narrow);
 }
 
@@ -1609,7 +1939,7 @@ __device__ __forceinline__ void tab_paths(const TabArgs &a, int eb, uint32_t *re
             b_hs = max(b_hs, red[4 * w + 3]);
         }
         int p, r;
-        decide_paths(eb, a_lo, a_hs, b_lo, b_hs, have, a.narrow, p, r);
+        decide_paths(eb, 0, a_lo, a_hs, b_lo, b_hs, have, a.narrow, p, r);
         red[4 * NW + 0] = uint32_t(p);
         red[4 * NW + 1] = uint32_t(r);
     }
@@ -1623,9 +1953,8 @@ template <int OP, int TM, int TN, int WR, int NW, int RL, int VAR>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(4, 4))) void tab_kernel(TabArgs args)
 {
     TabArgs a = args;
-    tab_tile_id(a.splits, a.tx, a.ty, a.tz);
     if constexpr (VAR == kTabNative) {
-        tab_body_native<OP, TM, TN, WR, NW>(a);
+        if (tab_tile_id(a)) tab_body_native<OP, TM, TN, WR, NW>(a);
         return;
     }
     const int eb = __builtin_amdgcn_readfirstlane(a.eb[0]);
@@ -1634,8 +1963,19 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(4, 4)))
         extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
         tab_paths<NW>(a, eb, reinterpret_cast<uint32_t *>(smem), self_path, self_rounded);
     }
+    const int path = VAR == kTabApproxSelf ? self_path : __builtin_amdgcn_readfirstlane(a.eb[1]);
+    if constexpr (RL == 7 && VAR == kTabApprox) {
+        if (path == 2 + kMmaAdd) {
+            tab_mma<OP, NW, kMmaAdd>(a);
+            return;
+        }
+        if (path == 2 + kMmaExact) {
+            tab_mma<OP, NW, kMmaExact>(a);
+            return;
+        }
+    }
+    if (!tab_tile_id(a)) return;
     if constexpr (RL == 7 && dot_cols_ok(TN) && WR == NW) {
-        const int path = VAR == kTabApproxSelf ? self_path : __builtin_amdgcn_readfirstlane(a.eb[1]);
         if (path == 1) {
             tab_body_dot<OP, TM, NW, TN>(a);
             return;
@@ -1699,6 +2039,8 @@ constexpr size_t tab_lds_bytes(int tn, int wr, int nw, int rl)
     const size_t sum = rl >= 8 ? tab_sum_lds_bytes(tnw, rl) : 0;
     b = b > dot ? b : dot;
     b = b > sum ? b : sum;
+    const size_t mma = rl == 7 ? mma_lds_bytes(nw) : 0;
+    b = b > mma ? b : mma;
     return b > hl ? b : hl;
 }
 

@@ -57,8 +57,21 @@ hipError_t tab_attributes()
 }
 
 template <int OP>
-hipError_t tab_launch(const Tile &t, int rl, int var, const TabArgs &a, dim3 grid, hipStream_t st)
+hipError_t tab_launch(const Tile &t, int rl, int var, const TabArgs &args, dim3 tiles, hipStream_t st)
 {
+    TabArgs a = args;
+    a.gx = int(tiles.x);
+    a.gy = int(tiles.y);
+    a.gz = int(tiles.z);
+    // the matrix-core bodies tile the result their own way: workgroups for whichever tiles are more
+    int64_t blocks = int64_t(tiles.x) * tiles.y * tiles.z;
+    if (rl == 7 && var == kTabApprox) {
+        const MmaTiles mt = mma_tiles(a.R, a.N, t.nw);
+        const int64_t mma = int64_t(mt.nrow) * mt.ncol * tiles.z;
+        if (mma > blocks) blocks = (mma + 7) / 8 * 8;  // a multiple of 8 keeps the XCD order
+    }
+    if (blocks * 64 * t.nw >= int64_t(1) << 32) return hipErrorInvalidConfiguration;
+    const dim3 grid{unsigned(blocks)};
     bool launched = false;
     auto run = [&](auto tm, auto tn, auto wr, auto nw, auto rl_c) {
         constexpr int TM = decltype(tm)::value, TN = decltype(tn)::value, WR = decltype(wr)::value;
