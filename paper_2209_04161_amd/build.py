@@ -16,9 +16,9 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 # (source, extra flags): the table kernels are compiled once per operation (0 GEMM, 1 forward,
-# 2 backward data, 3 backward weight), in parallel with the rest.
+# 2 backward data, 3 backward weight) and row-length class, in parallel with the rest.
 UNITS = [("amsim_kernels.hip", []), ("amsim_host.cpp", [])] + [
-    ("amsim_tab.hip", ["-DAMSIM_TAB_OP=%d" % op]) for op in range(4)]
+    ("amsim_tab.hip", ["-DAMSIM_TAB_OP=%d" % op, "-DAMSIM_TAB_WIDE=%d" % wide]) for wide in (0, 1) for op in range(4)]
 LIB = os.path.join(HERE, "libamsim.so")
 ARCH = os.environ.get("AMSIM_OFFLOAD_ARCH", "gfx950")
 FLAGS = ["--offload-arch=" + ARCH, "-O3", "-std=c++17", "-fPIC",

@@ -688,9 +688,11 @@ __global__ __launch_bounds__(256) void direct_gemm_kernel(const float *__restric
 // sums then added in group order.  G > 1 gives outputs with many splits more threads.  Workgroups
 // of 256 threads: thread (g, o) for g < G, o < 256 / G.
 __global__ __launch_bounds__(256) void reduce_splits_kernel(const float *__restrict__ part, int splits, int rows,
-                                                            int cols, float *__restrict__ C, int64_t ldc, int G)
+                                                            int cols, float *__restrict__ C, int64_t ldc, int G,
+                                                            const int *__restrict__ flags, int own_splits)
 {
     __shared__ float s_part[256];
+    if (flags != nullptr && flags[1] >= 3) splits = own_splits;  // uniform
     const int64_t total = int64_t(rows) * cols;
     const int opb = 256 / G;  // outputs per workgroup and pass
     const int g = int(threadIdx.x) / opb, ol = int(threadIdx.x) % opb;
@@ -1152,9 +1154,9 @@ __device__ __forceinline__ uint32_t block_or(uint32_t v, uint32_t *s4)
 }
 
 // Whether entry i = (ka << m) + kb is not the additive table's, (ka + kb) << (23 - m) (kMissAdd), or
-// not the exact product's of 1.ka and 1.kb (kMissExact), for 3 <= m <= 7 (the matrix-core bodies'
-// kinds kMmaAdd and kMmaExact; Mitchell's multiplier and the exact truncated product).
-constexpr uint32_t kMissAdd = 0x80000000u, kMissExact = 0x40000000u;
+// not the exact product's of 1.ka and 1.kb (kMissExact), for 3 <= m <= 11: the kinds kMmaAdd and
+// kMmaExact, Mitchell's multiplier and the exact truncated product.
+constexpr uint32_t kMissAdd = 0x80000000u, kMissExact = 0x40000000u, kMissSum = 0x20000000u;
 constexpr int kMissFlag = 16;  // of the flags' 64 words, one per table workgroup (table_jobs) from here
 __device__ __forceinline__ uint32_t table_misses(uint32_t entry, int i, int m)
 {
@@ -1267,9 +1269,10 @@ __device__ __forceinline__ void prep_table_body(const TablePrep &t, int bid, int
 }
 
 // Wide tables (M = 8..11, rows of 2^M entries, no bf16 path).  The pre-pass job, one word per
-// workgroup: the OR of the entries' low 16 mantissa bits, and bit 31 set when an entry (ka, kb)
-// differs from the entry of the same index sum s = ka + kb in row min(s, 2^M - 1) -- i.e. when the
-// table is not sum-indexed (T[ka][kb] = g(ka + kb)).
+// workgroup: the OR of the entries' low 16 mantissa bits, the kinds of table that the entries rule out
+// (table_misses), and kMissSum when an entry (ka, kb) differs from the entry of the same index sum
+// s = ka + kb in row min(s, 2^M - 1) -- i.e. when the table is not sum-indexed (T[ka][kb] =
+// g(ka + kb)).
 __device__ __forceinline__ void lut_low_bits_body(const TablePrep &t, int bid, int nblk)
 {
     __shared__ uint32_t s_low[4];
@@ -1279,7 +1282,8 @@ __device__ __forceinline__ void lut_low_bits_body(const TablePrep &t, int bid, i
         const uint32_t e = t.lut[i];
         const int s = (i >> t.m) + (i & (n - 1)), ka = min(s, n - 1);
         low |= e & 0xFFFFu;
-        if (((e ^ t.lut[(ka << t.m) + (s - ka)]) & 0x00FFFFFFu) != 0u) low |= 0x80000000u;
+        if (((e ^ t.lut[(ka << t.m) + (s - ka)]) & 0x00FFFFFFu) != 0u) low |= kMissSum;
+        low |= table_misses(e, i, t.m);
     }
     const uint32_t r = block_or(low, s_low);
     if (threadIdx.x == 0) t.part[bid] = r;
@@ -1288,7 +1292,7 @@ __device__ __forceinline__ void lut_low_bits_body(const TablePrep &t, int bid, i
 // Second launch for wide tables: the entry width from the nparts partial words, then the
 // transposed rows -- row kb (2^m entries of eb bytes) holds entry (ka, kb) at byte ka * eb --
 // through 64 x 64 LDS tiles (loads along kb, stores along ka).  Workgroup 0 writes flags[0] = eb,
-// flags[1] = 0 (no bf16 path for wide rows), flags[2], the exact path's product form, from
+// flags[1], an arithmetic body's path or 0 (no bf16 path for wide rows), flags[2], the exact path's product form, from
 // the decode statistics (n_a and n_b words; null for the native multiply), and flags[3] = 1 when
 // the table is sum-indexed.
 __global__ __launch_bounds__(256) void prep_rows_wide_kernel(const uint32_t *__restrict__ lut, int m,
@@ -1299,7 +1303,7 @@ __global__ __launch_bounds__(256) void prep_rows_wide_kernel(const uint32_t *__r
                                                              int *__restrict__ flags)
 {
     __shared__ uint32_t tile[64][65];
-    __shared__ uint32_t s_low[4], s_ahs[4], s_bhs[4];
+    __shared__ uint32_t s_low[4], s_alo[4], s_blo[4], s_ahs[4], s_bhs[4];
     uint32_t low = 0u;
     for (int i = threadIdx.x; i < nparts; i += 256) low |= part[i];
     const uint32_t lb = block_or(low, s_low);
@@ -1311,28 +1315,38 @@ __global__ __launch_bounds__(256) void prep_rows_wide_kernel(const uint32_t *__r
             stats_fold<256>(stats_a, n_a, alo, ahs);
             stats_fold<256>(stats_b, n_b, blo, bhs);
         }
+        alo = wave_min(alo);
+        blo = wave_min(blo);
         ahs = wave_max(ahs);
         bhs = wave_max(bhs);
         if ((threadIdx.x & 63) == 0) {
+            s_alo[threadIdx.x >> 6] = alo;
+            s_blo[threadIdx.x >> 6] = blo;
             s_ahs[threadIdx.x >> 6] = ahs;
             s_bhs[threadIdx.x >> 6] = bhs;
         }
         __syncthreads();
         if (threadIdx.x == 0) {
+            const uint32_t a_lo = min(min(s_alo[0], s_alo[1]), min(s_alo[2], s_alo[3]));
+            const uint32_t b_lo = min(min(s_blo[0], s_blo[1]), min(s_blo[2], s_blo[3]));
             const uint32_t a_hs = max(max(s_ahs[0], s_ahs[1]), max(s_ahs[2], s_ahs[3]));
             const uint32_t b_hs = max(max(s_bhs[0], s_bhs[1]), max(s_bhs[2], s_bhs[3]));
             int path, rounded;
-            decide_paths(eb, 0, 0u, a_hs, 0u, b_hs, have, narrow, path, rounded);
+            const int kind = (lb & kMissAdd) == 0u ? kMmaAdd : ((lb & kMissExact) == 0u ? kMmaExact : 0);
+            decide_paths(eb, kind, true, a_lo, a_hs, b_lo, b_hs, have, narrow, path, rounded);
             flags[0] = eb;
-            flags[1] = 0;
+            flags[1] = path;
             flags[2] = rounded;
-            flags[3] = (lb >> 31) == 0u ? 1 : 0;
+            flags[3] = (lb & kMissSum) == 0u ? 1 : 0;
         }
     }
+    if ((lb & kMissAdd) == 0u || (lb & kMissExact) == 0u) return;  // computed, no row is read (uniform)
     const int n = 1 << m, tiles_1d = n / 64;
     const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
     for (int t = blockIdx.x; t < tiles_1d * tiles_1d; t += gridDim.x) {
         const int ka0 = (t / tiles_1d) * 64, kb0 = (t % tiles_1d) * 64;
+        // a sum-indexed table's entries are read at kb = 0 and at ka = 2^m - 1 only
+        if ((lb & kMissSum) == 0u && kb0 != 0 && ka0 != n - 64) continue;
         for (int i = ty; i < 64; i += 4) tile[i][tx] = lut[size_t(ka0 + i) * n + kb0 + tx];  // [ka][kb]
         __syncthreads();
         for (int i = ty; i < 64; i += 4) {
@@ -1358,6 +1372,8 @@ __global__ __launch_bounds__(1024) void path_flags_kernel(const uint32_t *__rest
 {
     __shared__ uint32_t red[16][4];
     uint32_t alo = 255u, ahs = 0u, blo = 255u, bhs = 0u;
+    const uint32_t miss0 = int(threadIdx.x) < n_tab ? uint32_t(flags[kMissFlag + int(threadIdx.x)]) : 0u;
+    const int eb = flags[0];
     stats_fold<1024>(stats_a, n_a, alo, ahs);
     stats_fold<1024>(stats_b, n_b, blo, bhs);
     alo = wave_min(alo);
@@ -1365,6 +1381,8 @@ __global__ __launch_bounds__(1024) void path_flags_kernel(const uint32_t *__rest
     blo = wave_min(blo);
     bhs = wave_max(bhs);
     const int wave = int(threadIdx.x) >> 6;
+    const bool add = __builtin_amdgcn_ballot_w64((miss0 & kMissAdd) != 0u) == 0u;  // n_tab <= 16: the first wave's
+    const bool exact = __builtin_amdgcn_ballot_w64((miss0 & kMissExact) != 0u) == 0u;
     if ((threadIdx.x & 63) == 0) {
         red[wave][0] = alo;
         red[wave][1] = ahs;
@@ -1374,17 +1392,16 @@ __global__ __launch_bounds__(1024) void path_flags_kernel(const uint32_t *__rest
     __syncthreads();
     if (threadIdx.x == 0) {
         uint32_t a_lo = 255u, a_hs = 0u, b_lo = 255u, b_hs = 0u;
+#pragma unroll
         for (int w = 0; w < 16; ++w) {
             a_lo = min(a_lo, red[w][0]);
             a_hs = max(a_hs, red[w][1]);
             b_lo = min(b_lo, red[w][2]);
             b_hs = max(b_hs, red[w][3]);
         }
-        uint32_t miss = 0u;
-        for (int i = 0; i < n_tab; ++i) miss |= uint32_t(flags[kMissFlag + i]);
-        const int kind = (miss & kMissAdd) == 0u ? kMmaAdd : ((miss & kMissExact) == 0u ? kMmaExact : 0);
+        const int kind = add ? kMmaAdd : (exact ? kMmaExact : 0);
         int path, rounded;
-        decide_paths(flags[0], kind, a_lo, a_hs, b_lo, b_hs, true, narrow, path, rounded);
+        decide_paths(eb, kind, false, a_lo, a_hs, b_lo, b_hs, true, narrow, path, rounded);
         flags[1] = path;
         flags[2] = rounded;
     }
@@ -1454,14 +1471,16 @@ int ensure_attributes()
 }
 
 // Split reduction of `splits` partial results of rows x cols into C (leading dimension ldc).
-void launch_reduce(const float *part, int splits, int rows, int cols, float *C, int64_t ldc, hipStream_t st)
+// flags (or null): a call's path flags; own_splits partial results when a body with its own splits ran.
+void launch_reduce(const float *part, int splits, int rows, int cols, float *C, int64_t ldc, hipStream_t st,
+                   const int *flags = nullptr, int own_splits = 0)
 {
     const int64_t outputs = int64_t(rows) * cols;
     int G = 1;
     while (G < 32 && outputs * G < 65536 && splits >= 16 * G) G *= 2;
     const int64_t blocks = std::min<int64_t>(ceil_div(outputs, 256 / G), 65536);
     hipLaunchKernelGGL(reduce_splits_kernel, dim3(unsigned(blocks)), dim3(256), 0, st, part, splits, rows, cols, C, ldc,
-                       G);
+                       G, flags, own_splits);
 }
 
 int launch_status()
@@ -1600,6 +1619,12 @@ int run_prepass(const PrepJobs &j, const A &a, size_t lds, int var, int narrow, 
                            j.n_tab, j.t.flags);
     }
     return launch_status();
+}
+
+// The path flags the split reduction reads: only the variant that reads them has written them.
+const int *reduce_flags(const char *ws, const Plan &p, int var)
+{
+    return var == kTabApprox ? reinterpret_cast<const int *>(ws + p.off_eb) : nullptr;
 }
 
 // The pointers of a launch's arguments (the rest is the plan's geometry, g).
@@ -1882,7 +1907,8 @@ int gemm_run(const Mode &md, int trans_a, int trans_b, int64_t m, int64_t n, int
     }
     if (rc != AMSIM_OK) return AMSIM_ERR_HIP;
     if (p.splits > 1) {
-        launch_reduce(reinterpret_cast<const float *>(ws + p.off_part), p.splits, int(m), int(n), C, ldc, st);
+        launch_reduce(reinterpret_cast<const float *>(ws + p.off_part), p.splits, int(m), int(n), C, ldc, st,
+                      reduce_flags(ws, p, var), p.own_splits);
         if (launch_status() != AMSIM_OK) return AMSIM_ERR_HIP;
     }
     return AMSIM_OK;
@@ -1995,7 +2021,8 @@ int fwd_core(const Mode &md, const amsim_conv2d *desc, const float *x, const flo
                  : AMSIM_ERR_HIP;
     }
     if (rc != AMSIM_OK || p.splits == 1) return rc;
-    launch_reduce(reinterpret_cast<const float *>(ws + p.off_part), p.splits, int(rows), s.co, y, int64_t(s.co), st);
+    launch_reduce(reinterpret_cast<const float *>(ws + p.off_part), p.splits, int(rows), s.co, y, int64_t(s.co), st,
+                  reduce_flags(ws, p, var), p.own_splits);
     return launch_status();
 }
 
@@ -2045,7 +2072,7 @@ int bwd_data_run(const Mode &md, const amsim_conv2d *desc, const Plan &p, const 
     if (rc != AMSIM_OK) return rc;
     if (p.splits > 1) {
         launch_reduce(reinterpret_cast<const float *>(ws + p.off_part), p.splits, s.n * s.h * s.w, s.ci, dx,
-                      int64_t(s.ci), st);
+                      int64_t(s.ci), st, reduce_flags(ws, p, var), p.own_splits);
         if (launch_status() != AMSIM_OK) return AMSIM_ERR_HIP;
     }
     if (fixup && s.sh * s.sw > 1) {  // the taps outside each output's stride phase (dilation zeros)
@@ -2135,7 +2162,8 @@ int conv_bwd_weight_run(const Mode &md, const amsim_conv2d *desc, const float *x
     }
     if (rc != AMSIM_OK) return AMSIM_ERR_HIP;
     if (p.splits > 1) {
-        launch_reduce(reinterpret_cast<const float *>(ws + p.off_part), p.splits, R, s.co, dw, int64_t(s.co), st);
+        launch_reduce(reinterpret_cast<const float *>(ws + p.off_part), p.splits, R, s.co, dw, int64_t(s.co), st,
+                      reduce_flags(ws, p, var), p.own_splits);
         return launch_status();
     }
     return AMSIM_OK;

@@ -75,6 +75,8 @@ struct TabArgs {
     int m;               // mantissa bits of the table index
     int chunk;           // steps per reduction chunk (8)
     int chunks_per_split;  // reduction chunks per split
+    int own_c;             // bodies with tiles of their own: tile width (own_cols),
+    int own_splits, own_cps;  // splits and chunks per split
     int64_t out_elems;   // elements of one split's partial result (splits > 1)
     int Mp, K;           // GEMM
     ConvShape s;
@@ -110,6 +112,34 @@ __device__ __forceinline__ bool tab_tile_id(TabArgs &a)
     a.ty = int(rest % gy);
     a.tx = int((rest / gy) % gx);
     a.tz = int(ph * uint32_t(a.splits) + rest / (gx * gy));
+    return true;
+}
+
+// Columns of such a body's tiles, of width code c: the matrix-core bodies' WC (4 or 2) or the arithmetic
+// bodies' TN (8 or 4).
+__host__ __device__ constexpr int own_cols(int c) { return 16 * c; }
+
+// The workgroup's tile (tx, ty) of a body that tiles and splits the result its own way, nrow x ncol
+// tiles per phase and split, a.tz and the body's splits in a: contiguous ranges of tiles per XCD, in tab_tile_id's order.  False for a
+// workgroup past the last tile.
+__device__ __forceinline__ bool own_tile(TabArgs &a, int nrow, int ncol, int &tx, int &ty)
+{
+    const uint32_t phases = uint32_t(a.gz) / uint32_t(a.splits);
+    a.splits = a.own_splits;
+    a.chunks_per_split = a.own_cps;
+    const uint32_t tiles = uint32_t(nrow) * uint32_t(ncol) * phases * uint32_t(a.splits);
+    uint32_t id = blockIdx.x;
+    if (gridDim.x % 8u == 0u) {
+        const uint32_t per = (tiles + 7u) / 8u;
+        if (id / 8u >= per) return false;
+        id = (id % 8u) * per + id / 8u;
+    }
+    if (id >= tiles) return false;
+    const uint32_t ph = id % phases, rest = id / phases;
+    ty = int(rest % uint32_t(ncol));
+    const int rest2 = int(rest / uint32_t(ncol));
+    tx = rest2 % nrow;
+    a.tz = int(ph) * a.splits + rest2 / nrow;
     return true;
 }
 
@@ -1376,18 +1406,7 @@ __device__ __forceinline__ f32x4_t mma_16x16x32(u32x4 x, u32x4 y, f32x4_t c)
 }
 
 // A workgroup of NW waves: 32 NW rows x 16 WC columns, a wave 32 WC rows (2 WC blocks of 16) x 16
-// columns.  WC = 4 where there are more than 32 columns, so that a staged row serves 64 columns, else 2.
-struct MmaTiles {
-    int wc, nrow, ncol;
-};
-__host__ __device__ __forceinline__ MmaTiles mma_tiles(int rows, int cols, int nw)
-{
-    MmaTiles t;
-    t.wc = cols > 32 ? 4 : 2;
-    t.nrow = (rows + 32 * nw - 1) / (32 * nw);
-    t.ncol = (cols + 16 * t.wc - 1) / (16 * t.wc);
-    return t;
-}
+// columns, WC = 4 or 2 (a.own_c).
 
 // LDS: two slabs of 32 steps (4 reduction chunks), each [row][4 x 16 bytes] of the first operand, the
 // 16-byte pieces of a row permuted by its bits 2..3 so that 16 rows' pieces cover the banks, and
@@ -1398,7 +1417,7 @@ constexpr int mma_b_bytes(int wc) { return 2 * 4 * 16 * wc * 16; }
 constexpr size_t mma_lds_bytes(int nw) { return 2 * size_t(mma_a_bytes(nw) + mma_b_bytes(4)) + 256; }
 
 template <int OP, int NW, int WC, int KIND>
-__device__ __forceinline__ void tab_body_mma(const TabArgs &a0, const MmaTiles &mt)
+__device__ __forceinline__ void tab_body_mma(const TabArgs &a0)
 {
     constexpr int NT = 64 * NW;
     constexpr int RT = 2 * WC, WR = NW / WC;
@@ -1408,21 +1427,8 @@ __device__ __forceinline__ void tab_body_mma(const TabArgs &a0, const MmaTiles &
     constexpr int BPH = (BU / 2 + NT - 1) / NT;  // of them per thread and half of the slab's columns' work
     static_assert(WR * WC == NW && NT == 2 * ROWS, "workgroup shape");
     TabArgs a = a0;
-    // this workgroup's tile: contiguous ranges of tiles per XCD, in tab_tile_id's order
-    const uint32_t tiles = uint32_t(mt.nrow) * uint32_t(mt.ncol) * uint32_t(a.gz);
-    uint32_t id = blockIdx.x;
-    if (gridDim.x % 8u == 0u) {
-        const uint32_t per = (tiles + 7u) / 8u;
-        if (id / 8u >= per) return;
-        id = (id % 8u) * per + id / 8u;
-    }
-    if (id >= tiles) return;
-    const uint32_t phases = uint32_t(a.gz) / uint32_t(a.splits);
-    const uint32_t ph = id % phases, rest = id / phases;
-    const int ty = int(rest % uint32_t(mt.ncol)), rest2 = int(rest / uint32_t(mt.ncol));
-    const int tx = rest2 % mt.nrow;
-    a.tz = int(ph) * a.splits + rest2 / mt.nrow;
-
+    int tx, ty;
+    if (!own_tile(a, (a.R + ROWS - 1) / ROWS, (a.N + COLS - 1) / COLS, tx, ty)) return;
     const int R = tab_rows<OP>(a);
     if (tx * ROWS >= R) return;  // uniform over the workgroup
     const int lane = threadIdx.x & 63, n = lane & 15, g = lane >> 4;
@@ -1627,11 +1633,209 @@ __device__ __forceinline__ void tab_body_mma(const TabArgs &a0, const MmaTiles &
 template <int OP, int NW, int KIND>
 __device__ __forceinline__ void tab_mma(const TabArgs &a)
 {
-    const MmaTiles mt = mma_tiles(a.R, a.N, NW);
-    if (mt.wc == 4)
-        tab_body_mma<OP, NW, 4, KIND>(a, mt);
+    if (a.own_c == 4)
+        tab_body_mma<OP, NW, 4, KIND>(a);
     else
-        tab_body_mma<OP, NW, 2, KIND>(a, mt);
+        tab_body_mma<OP, NW, 2, KIND>(a);
+}
+
+// ------------------------------------------------- additive and exact-product wide tables (M = 8..11)
+// The kinds of the matrix-core bodies (above), with products formed in FP32 on the vector ALU: no gather,
+// where the sum-indexed body above waits on one random 4-byte LDS read per product and the exact path
+// stages rows of 2^M entries.  a and b are the operands cut to M mantissa bits, pa and pb their heads.
+//   ROUNDED = false, in the operand window (decide_paths), no product out of range:
+//     kMmaAdd     t = v * pa has the bit pattern bits(a) + (kb << (23 - M)); acc = fma(t, pb, acc).
+//                 A zero a has t below 2^-126, a denormal, which the fma reads as zero.
+//     kMmaExact   acc = fma(a, b, acc): a * b is exact (at most 24 bits).
+//   ROUNDED = true, any operands and formats: the exact path's arithmetic (tab_body) with the factor
+//     v' computed instead of gathered, as an integer sum of bit patterns (kMmaAdd) or as the exact
+//     product of the two significands (kMmaExact, at most 24 bits): c = v' * (pa * pb), then
+//     acc = fma(c * su, sd, acc).
+//
+// Both operands go through LDS, double-buffered slabs of KS steps, [step][row] words of a and
+// [step][column] words of b, one or two per operand: a, or its significand and head; (kb, pb) or b, or
+// b's significand and head.  A workgroup of NW waves computes 32 NW rows by 16 TN columns, a lane 8
+// rows by TN columns: TN = 8 (waves of 64 x 64) or 4 (waves of 32 rows by all columns; a.own_c).  Padding steps are +0 against -0, a product of -0, which leaves every sum and its sign.
+// What bounds it: the vector ALU; FP32 multiplies and fmas issue at twice the rate of integer
+// additions here.  Measured on MI355X, before (the sum-indexed body or staged rows) and after: the
+// GEMM 4096^3 at M = 11 with Mitchell's table 13.4 -> 2.6 ms, 2048^3 with the exact product 3.92 ->
+// 0.44 ms, 1024^3 at M = 10 in a (1, 5, 10) format 0.48 -> 0.13 ms.
+template <int KIND, bool ROUNDED>
+struct ArithShape {
+    static constexpr int KS = ROUNDED ? 8 : 16;                            // steps per slab
+    static constexpr int AW = ROUNDED ? 2 : 1;                             // words per element of a
+    static constexpr int BW = ROUNDED || KIND == kMmaAdd ? 2 : 1;          // and of b
+    static constexpr int words(int nw, int tn) { return KS * (32 * nw * AW + 16 * tn * BW); }
+};
+constexpr size_t arith_lds_bytes(int nw)
+{
+    constexpr int w1 = 4 * 2;  // two buffers of words
+    const size_t a = size_t(ArithShape<kMmaAdd, false>::words(nw, 8)) * w1;
+    const size_t b = size_t(ArithShape<kMmaAdd, true>::words(nw, 8)) * w1;
+    return a > b ? a : b;
+}
+
+template <int OP, int NW, int TN, int KIND, bool ROUNDED>
+__device__ __forceinline__ void tab_body_arith(const TabArgs &a0)
+{
+    using Shape = ArithShape<KIND, ROUNDED>;
+    constexpr int NT = 64 * NW;
+    constexpr int ROWS = 32 * NW, COLS = 16 * TN, KS = Shape::KS, AW = Shape::AW, BW = Shape::BW;
+    constexpr int LC = TN == 8 ? 8 : 16;           // lanes along columns
+    constexpr int WROWS = TN == 8 ? 64 : 32;       // rows of a wave
+    constexpr int WC = TN == 8 ? 2 : 1;            // waves along columns
+    constexpr int BUFW = Shape::words(NW, TN);     // words of a buffer
+    constexpr int RPT = KS / 4;                    // staged records per thread and slab: steps sc * KS / 2 on
+    constexpr int BPT = KS * COLS / NT;            // staged second-operand words
+    static_assert(NT == 2 * ROWS && BPT * NT == KS * COLS && WC * (ROWS / WROWS) == NW, "workgroup shape");
+    TabArgs a = a0;
+    int tx, ty;
+    if (!own_tile(a, (a.R + ROWS - 1) / ROWS, (a.N + COLS - 1) / COLS, tx, ty)) return;
+    const int R = tab_rows<OP>(a);
+    if (tx * ROWS >= R) return;  // uniform over the workgroup
+    const int lane = threadIdx.x & 63, lc = lane % LC, lr = lane / LC;
+    const int wave = wave_id();
+    const int roww = tx * ROWS, colw = ty * COLS;
+    const int rl0 = (wave / WC) * WROWS + lr * 8;       // the lane's first row in the workgroup's
+    const int cl0 = (wave % WC) * (TN * LC) + lc * TN;  // and column
+    const bool live = roww + (wave / WC) * WROWS < R && colw + (wave % WC) * (TN * LC) < a.N;  // wave-uniform
+
+    const int count = tab_count<OP>(a), ch = a.chunk;  // ch = 8 steps
+    const int cpt = (count + ch - 1) / ch;
+    const int q_total = tab_taps<OP>(a) * cpt;
+    const int q0 = tab_split(a) * a.chunks_per_split, q1 = min(q_total, q0 + a.chunks_per_split);
+    const int m = a.m;
+
+    const int srow = int(threadIdx.x) % ROWS, s0 = __builtin_amdgcn_readfirstlane(int(threadIdx.x) / ROWS) * (KS / 2);
+    const __amdgpu_buffer_rsrc_t arec =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t *>(a.A), 0, int(a.a_bytes), 0x00020000);
+    const uint32_t aoff = uint32_t(roww + srow < R ? tab_row_rec<OP>(a, roww + srow) : 0) * kPairRecordBytes;
+    u32x3 sa[RPT];
+    int sa_n = 0;  // how many of the staged steps exist
+    uint32_t sb[BPT];
+    auto fetch = [&](int qs) __attribute__((always_inline)) {
+        {
+            const int q = qs + s0 / 8, qq = min(q, q1 - 1);  // past the end: loads in bounds, not used
+            const int tap = OP == OP_GEMM ? 0 : qq / cpt;
+            const TabTap tp = tab_tap_raw<OP>(a, tap);
+            const int j0 = (qq - tap * cpt) * ch + s0 % 8;
+            sa_n = q < q1 ? count - j0 : 0;
+#pragma unroll
+            for (int p = 0; p < RPT; ++p) {
+                const uint32_t so = __builtin_amdgcn_readfirstlane(
+                    uint32_t(tp.pbase + min(j0 / 2 + p, (count - 1) / 2) * tp.ustride) * kPairRecordBytes);
+                sa[p] = __builtin_amdgcn_raw_buffer_load_b96(arec, aoff, so, 0);
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < BPT; ++i) {
+            const int u = int(threadIdx.x) + i * NT, col = colw + u % COLS, st = u / COLS, q = qs + st / 8;
+            sb[i] = 0x80000000u;
+            if (q < q1) {
+                const int tap = OP == OP_GEMM ? 0 : q / cpt;
+                const int j = (q - tap * cpt) * ch + st % 8;
+                if (j < count && col < a.Np) sb[i] = Bd_word(a, tab_tap_raw<OP>(a, tap).bbase + j, col);
+            }
+        }
+    };
+    const uint32_t one = 0x3F800000u;
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    auto commit = [&](int buf) __attribute__((always_inline)) {
+        uint32_t *ab = reinterpret_cast<uint32_t *>(smem) + buf * BUFW, *bb = ab + KS * ROWS * AW;
+#pragma unroll
+        for (int p = 0; p < RPT; ++p)
+#pragma unroll
+            for (int e = 0; e < 2; ++e) {
+                const int st = s0 + 2 * p + e;
+                const bool in = 2 * p + e < sa_n;
+                const uint32_t head = e == 0 ? sa[p].y << 16 : sa[p].y & 0xFFFF0000u;
+                const uint32_t ka = (e == 0 ? sa[p].x : sa[p].z) << (19 - m);  // index words ka << 4
+                if constexpr (ROUNDED) {
+                    ab[st * ROWS + srow] = in ? one + a.vadd + ka : one;
+                    ab[(KS + st) * ROWS + srow] = in ? head : 0u;
+                } else {
+                    ab[st * ROWS + srow] = in ? head + ka : 0u;
+                }
+            }
+#pragma unroll
+        for (int i = 0; i < BPT; ++i) {
+            const int u = int(threadIdx.x) + i * NT;
+            const uint32_t kb = (sb[i] & kIdxMask) << (23 - 2 * m), head = sb[i] & kHeadMask;  // kb << M in the word
+            if constexpr (ROUNDED || KIND == kMmaAdd) {
+                bb[u] = KIND == kMmaAdd ? kb : one + kb;
+                bb[KS * COLS + u] = head;
+            } else {
+                bb[u] = head + kb;
+            }
+        }
+    };
+    float acc[8][TN];
+    init_acc(acc);
+    int buf = 0;
+    bool have = false;
+    for (int qs = q0;; qs += KS / 8) {  // slab qs is staged while the one before it is computed
+        const bool more = qs < q1;
+        if (more) fetch(qs);
+        if (live && have) {
+            const uint32_t *ar = reinterpret_cast<const uint32_t *>(smem) + (buf ^ 1) * BUFW + rl0;
+            const uint32_t *br = reinterpret_cast<const uint32_t *>(smem) + (buf ^ 1) * BUFW + KS * ROWS * AW + cl0;
+#pragma unroll 2
+            for (int st = 0; st < KS; ++st) {
+                uint32_t av[AW][8], bv[BW][TN];
+#pragma unroll
+                for (int i = 0; i < AW; ++i)
+#pragma unroll
+                    for (int r = 0; r < 8; ++r) av[i][r] = ar[(i * KS + st) * ROWS + r];
+#pragma unroll
+                for (int i = 0; i < BW; ++i)
+#pragma unroll
+                    for (int t = 0; t < TN; ++t) bv[i][t] = br[(i * KS + st) * COLS + t];
+#pragma unroll
+                for (int t = 0; t < TN; ++t)
+#pragma unroll
+                    for (int r = 0; r < 8; ++r) {
+                        const float x = __uint_as_float(av[0][r]), y = __uint_as_float(bv[0][t]);
+                        if constexpr (ROUNDED) {
+                            const float v = KIND == kMmaAdd ? __uint_as_float(av[0][r] + bv[0][t]) : x * y;
+                            const float c = v * (__uint_as_float(av[AW - 1][r]) * __uint_as_float(bv[BW - 1][t]));
+                            acc[r][t] = __builtin_fmaf(c * a.su, a.sd, acc[r][t]);
+                        } else if constexpr (KIND == kMmaAdd) {
+                            acc[r][t] = __builtin_fmaf(__uint_as_float(av[0][r] + bv[0][t]),
+                                                       __uint_as_float(bv[BW - 1][t]), acc[r][t]);
+                        } else {
+                            acc[r][t] = __builtin_fmaf(x, y, acc[r][t]);
+                        }
+                    }
+            }
+        }
+        if (!more) break;
+        commit(buf);
+        __syncthreads();
+        buf ^= 1;
+        have = true;
+    }
+    if (!live) return;
+    float *out = a.out + int64_t(tab_split(a)) * a.out_elems;
+#pragma unroll
+    for (int r = 0; r < 8; ++r) {
+        const int row = roww + rl0 + r;
+        if (row >= R) continue;
+        float *dst = out + tab_row_out<OP>(a, row);
+#pragma unroll
+        for (int t = 0; t < TN; ++t) {
+            const int col = colw + cl0 + t;
+            if (col < a.N) dst[col] = acc[r][t];
+        }
+    }
+}
+
+template <int OP, int NW, int KIND, bool ROUNDED>
+__device__ __forceinline__ void tab_arith(const TabArgs &a)
+{
+    if (a.own_c == 8)
+        tab_body_arith<OP, NW, 8, KIND, ROUNDED>(a);
+    else
+        tab_body_arith<OP, NW, 4, KIND, ROUNDED>(a);
 }
 
 // ------------------------------------------------------- bf16 hi/lo path (2-byte tables)
@@ -1872,8 +2076,10 @@ __device__ __forceinline__ int exact_needs_rounded_products(bool have_stats, boo
 //   path 3, in path 1's window, Ea + carry below 255 too: an additive table (kind kMmaAdd);
 //   path 4, in path 1's window: the exact product (kind kMmaExact);
 //   path 0, the exact path, whose product form is `rounded`.
+// With wide tables (rows of 256 entries or more) paths 3 and 4 are the arithmetic bodies of the two
+// kinds, 5 and 6 (4 + kind) their rounded form for any other operands, and there is no path 1 or 2.
 // have: the decode passes recorded statistics (not for the native multiply).
-__device__ __forceinline__ void decide_paths(int eb, int kind, uint32_t a_lo, uint32_t a_hs, uint32_t b_lo, uint32_t b_hs,
+__device__ __forceinline__ void decide_paths(int eb, int kind, bool wide, uint32_t a_lo, uint32_t a_hs, uint32_t b_lo, uint32_t b_hs,
                                              bool have, int narrow, int &path, int &rounded)
 {
     const uint32_t a_hi = a_hs & 0xFFu, b_hi = b_hs & 0xFFu;
@@ -1884,6 +2090,7 @@ __device__ __forceinline__ void decide_paths(int eb, int kind, uint32_t a_lo, ui
     if (kind == kMmaAdd && window && a_hi <= 253u) path = 3;
     if (kind == kMmaExact && window) path = 4;
     if (narrow) path = 0;
+    if (wide) path = path >= 3 ? path : (kind != 0 ? 4 + kind : 0);
     rounded = exact_needs_rounded_products(have, special, a_hi, b_hi, narrow);
 }
 
@@ -1939,7 +2146,7 @@ __device__ __forceinline__ void tab_paths(const TabArgs &a, int eb, uint32_t *re
             b_hs = max(b_hs, red[4 * w + 3]);
         }
         int p, r;
-        decide_paths(eb, 0, a_lo, a_hs, b_lo, b_hs, have, a.narrow, p, r);
+        decide_paths(eb, 0, false, a_lo, a_hs, b_lo, b_hs, have, a.narrow, p, r);
         red[4 * NW + 0] = uint32_t(p);
         red[4 * NW + 1] = uint32_t(r);
     }
@@ -1971,6 +2178,19 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(4, 4)))
         }
         if (path == 2 + kMmaExact) {
             tab_mma<OP, NW, kMmaExact>(a);
+            return;
+        }
+    }
+    if constexpr (RL >= 8) {
+        if (path >= 3) {
+            if (path == 3)
+                tab_arith<OP, NW, kMmaAdd, false>(a);
+            else if (path == 4)
+                tab_arith<OP, NW, kMmaExact, false>(a);
+            else if (path == 5)
+                tab_arith<OP, NW, kMmaAdd, true>(a);
+            else
+                tab_arith<OP, NW, kMmaExact, true>(a);
             return;
         }
     }
@@ -2036,7 +2256,8 @@ constexpr size_t tab_lds_bytes(int tn, int wr, int nw, int rl)
     b = tab_exact_lds_bytes(tnw, rl, 4) > b ? tab_exact_lds_bytes(tnw, rl, 4) : b;
     const size_t dot = (rl == 7 && dot_cols_ok(tn) && wr == nw) ? size_t(2) * dot_slab_steps(nw) * kDotStepBytes : 0;
     const size_t hl = (rl == 7 && tn == 8 && (nw == 8 || nw == 4) && wr == nw) ? size_t(2) * nw * kHlStepBytes : 0;
-    const size_t sum = rl >= 8 ? tab_sum_lds_bytes(tnw, rl) : 0;
+    const size_t arith = rl >= 8 ? arith_lds_bytes(nw) : 0;
+    const size_t sum0 = rl >= 8 ? tab_sum_lds_bytes(tnw, rl) : 0, sum = sum0 > arith ? sum0 : arith;
     b = b > dot ? b : dot;
     b = b > sum ? b : sum;
     const size_t mma = rl == 7 ? mma_lds_bytes(nw) : 0;
@@ -2097,13 +2318,26 @@ static_assert(tab_cands_listed(kTabCands, 7, 7) && tab_cands_listed(kWideCands, 
                   tab_cands_listed(kWide11Cands, 11, 11),
               "a tile candidate is missing from AMSIM_FOR_TAB_TILES");
 
-// Per operation (defined in amsim_tab.hip, one instantiation per operation): raise the dynamic
-// LDS limit of every instantiated tile's kernel and check that none uses static LDS; launch the
-// kernel of tile t with rows of 2^rl entries and variant var (kTabNative and kTabApproxSelf: rl = 7).  Both return the first HIP error, and the launch
-// hipErrorInvalidConfiguration for a tile that is not instantiated.
+// Per operation (defined in amsim_tab.hip, one instantiation per operation and row-length class: WIDE 0
+// rows of 128 entries, 1 longer ones): raise the dynamic LDS limit of every instantiated tile's
+// kernel and check that none uses static LDS; launch the kernel of tile t with rows of 2^rl entries
+// and variant var (kTabNative and kTabApproxSelf: rl = 7).  Both return the first HIP error, and the
+// launch hipErrorInvalidConfiguration for a tile that is not instantiated.
+template <int OP, int WIDE>
+hipError_t tab_attributes_of();
+template <int OP, int WIDE>
+hipError_t tab_launch_of(const Tile &t, int rl, int var, const TabArgs &a, dim3 tiles, hipStream_t st);
+
 template <int OP>
-hipError_t tab_attributes();
+hipError_t tab_attributes()
+{
+    const hipError_t e = tab_attributes_of<OP, 0>(), w = tab_attributes_of<OP, 1>();
+    return e != hipSuccess ? e : w;
+}
 template <int OP>
-hipError_t tab_launch(const Tile &t, int rl, int var, const TabArgs &a, dim3 grid, hipStream_t st);
+hipError_t tab_launch(const Tile &t, int rl, int var, const TabArgs &a, dim3 tiles, hipStream_t st)
+{
+    return rl == 7 ? tab_launch_of<OP, 0>(t, rl, var, a, tiles, st) : tab_launch_of<OP, 1>(t, rl, var, a, tiles, st);
+}
 
 }  // namespace amsim_detail

@@ -1,11 +1,14 @@
 // amsim_tab.hip -- the table kernels of one operation, AMSIM_TAB_OP (0 GEMM, 1 forward,
-// 2 backward data, 3 backward weight; set by the build, which compiles this file once per
-// operation so that the four instantiation sets build in parallel), with their launch and
-// attribute set-up.
+// 2 backward data, 3 backward weight), on rows of 128 entries (AMSIM_TAB_WIDE = 0) or of 256 and more
+// (1), with their launch and attribute set-up.  The build sets both and compiles this file once for
+// each, so that the eight instantiation sets build in parallel.
 #include "amsim_tab.h"
 
 #ifndef AMSIM_TAB_OP
 #error "AMSIM_TAB_OP must name the operation (0..3)"
+#endif
+#ifndef AMSIM_TAB_WIDE
+#error "AMSIM_TAB_WIDE must choose the row lengths (0, 1)"
 #endif
 
 namespace amsim_detail __attribute__((visibility("hidden"))) {
@@ -29,11 +32,13 @@ template <typename F>
 void dispatch_tab_tile(const Tile &t, int rl, F &&f)
 {
 #define X(TM, TN, WR, NW, RL)                                                             \
-    if (t.tm == TM && t.tn == TN && t.wr == WR && t.nw == NW && rl == RL) {               \
-        f(std::integral_constant<int, TM>{}, std::integral_constant<int, TN>{},           \
-          std::integral_constant<int, WR>{}, std::integral_constant<int, NW>{},           \
-          std::integral_constant<int, RL>{});                                             \
-        return;                                                                           \
+    if constexpr ((RL > 7) == (AMSIM_TAB_WIDE != 0)) {                                    \
+        if (t.tm == TM && t.tn == TN && t.wr == WR && t.nw == NW && rl == RL) {           \
+            f(std::integral_constant<int, TM>{}, std::integral_constant<int, TN>{},       \
+              std::integral_constant<int, WR>{}, std::integral_constant<int, NW>{},       \
+              std::integral_constant<int, RL>{});                                         \
+            return;                                                                       \
+        }                                                                                 \
     }
     AMSIM_FOR_TAB_TILES(X)
 #undef X
@@ -41,13 +46,14 @@ void dispatch_tab_tile(const Tile &t, int rl, F &&f)
 
 }  // namespace
 
-template <int OP>
-hipError_t tab_attributes()
+template <int OP, int WIDE>
+hipError_t tab_attributes_of()
 {
     hipError_t err = hipSuccess;
 #define X(TM, TN, WR, NW, RL)                                                                              \
-    allow_lds(tab_kernel<OP, TM, TN, WR, NW, RL, kTabApprox>, tab_lds_bytes(TN, WR, NW, RL), err);          \
-    if constexpr (RL == 7) {                                                                                \
+    if constexpr ((RL > 7) == (WIDE != 0))                                                                  \
+        allow_lds(tab_kernel<OP, TM, TN, WR, NW, RL, kTabApprox>, tab_lds_bytes(TN, WR, NW, RL), err);          \
+    if constexpr (RL == 7 && WIDE == 0) {                                                                   \
         allow_lds(tab_kernel<OP, TM, TN, WR, NW, 7, kTabNative>, tab_native_lds_bytes(TN, WR, NW), err);    \
         allow_lds(tab_kernel<OP, TM, TN, WR, NW, 7, kTabApproxSelf>, tab_lds_bytes(TN, WR, NW, 7), err);    \
     }
@@ -56,19 +62,21 @@ hipError_t tab_attributes()
     return err;
 }
 
-template <int OP>
-hipError_t tab_launch(const Tile &t, int rl, int var, const TabArgs &args, dim3 tiles, hipStream_t st)
+template <int OP, int WIDE>
+hipError_t tab_launch_of(const Tile &t, int rl, int var, const TabArgs &args, dim3 tiles, hipStream_t st)
 {
     TabArgs a = args;
     a.gx = int(tiles.x);
     a.gy = int(tiles.y);
     a.gz = int(tiles.z);
-    // the matrix-core bodies tile the result their own way: workgroups for whichever tiles are more
+    // the bodies of additive and exact-product tables tile the result their own way: workgroups for
+    // whichever tiles are more
     int64_t blocks = int64_t(tiles.x) * tiles.y * tiles.z;
-    if (rl == 7 && var == kTabApprox) {
-        const MmaTiles mt = mma_tiles(a.R, a.N, t.nw);
-        const int64_t mma = int64_t(mt.nrow) * mt.ncol * tiles.z;
-        if (mma > blocks) blocks = (mma + 7) / 8 * 8;  // a multiple of 8 keeps the XCD order
+    if (var == kTabApprox) {
+        const int rows = 32 * t.nw, cols = own_cols(a.own_c);
+        const int64_t own = (int64_t(a.R) + rows - 1) / rows * ((int64_t(a.N) + cols - 1) / cols) *
+                            (int64_t(tiles.z) / a.splits * a.own_splits);
+        if (own > blocks) blocks = (own + 7) / 8 * 8;  // a multiple of 8 keeps the XCD order
     }
     if (blocks * 64 * t.nw >= int64_t(1) << 32) return hipErrorInvalidConfiguration;
     const dim3 grid{unsigned(blocks)};
@@ -100,7 +108,7 @@ hipError_t tab_launch(const Tile &t, int rl, int var, const TabArgs &args, dim3 
     return launched ? hipGetLastError() : hipErrorInvalidConfiguration;
 }
 
-template hipError_t tab_attributes<AMSIM_TAB_OP>();
-template hipError_t tab_launch<AMSIM_TAB_OP>(const Tile &, int, int, const TabArgs &, dim3, hipStream_t);
+template hipError_t tab_attributes_of<AMSIM_TAB_OP, AMSIM_TAB_WIDE>();
+template hipError_t tab_launch_of<AMSIM_TAB_OP, AMSIM_TAB_WIDE>(const Tile &, int, int, const TabArgs &, dim3, hipStream_t);
 
 }  // namespace amsim_detail

@@ -127,3 +127,59 @@ def test_convolution_passes_match_general_path(B, model, case):
                          (B.approx_conv2d_bwd_weight, (dx, ddy), oracle.conv2d_bwd_weight(mid, m, d, x, dy))):
         for lut, what in zip(_tables(B, model, m), ("matrix cores", "general path")):
             assert_within_tolerance(host(fn(d, *ins, lut, m)), *ref, "%s, %s" % (fn.__name__, what))
+
+
+WIDE = [  # m, n, k, trans_a, trans_b: the arithmetic bodies' tiles are 128 or 256 rows, 64 or 128 columns
+    (2, 2, 2, False, False), (127, 63, 15, False, True), (257, 65, 17, True, False), (130, 129, 33, True, True),
+    (300, 7, 1000, False, False), (33, 300, 9, False, False),
+]
+
+
+@pytest.mark.parametrize("model", sorted(MODELS))
+@pytest.mark.parametrize("e_bits,exps", [(8, (100, 151)), (8, (1, 255)), (5, (110, 143))])
+@pytest.mark.parametrize("case", range(len(WIDE)))
+def test_wide_tables_match_general_path(B, model, e_bits, exps, case):
+    """M = 8..11: inside the operand window, outside it (products that under- and overflow) and in a
+    (1, 5, M) format.  Class and sign of Inf and NaN sums as the oracle's on either path."""
+    m, n, k, ta, tb = WIDE[case]
+    mb = (8, 11, 9, 10)[(case + len(model)) % 4]
+    rng = np.random.default_rng(1000 + case)
+
+    def operand(shape, zeros):
+        x = _operand(rng, shape, mb, zeros).view(np.uint32)
+        e = rng.integers(exps[0], exps[1], shape).astype(np.uint32) << np.uint32(23)
+        return np.where(x << np.uint32(1) == 0, x, (x & np.uint32(0x807FFFFF)) | e).astype(np.uint32).view(np.float32)
+
+    a, b = operand((m, k), 0.2), operand((k, n), 0.1)
+    a[m // 2] = -0.0
+    da = torch.from_numpy(np.ascontiguousarray(a.T if ta else a)).cuda()
+    db = torch.from_numpy(np.ascontiguousarray(b.T if tb else b)).cuda()
+    ref, S = oracle.gemm(MODELS[model], mb, a, b, e_bits=e_bits)
+    for lut, what in zip(_tables(B, model, mb), ("computed", "general path")):
+        got = host(B.approx_gemm_ex(da, db, lut, mb, trans_a=ta, trans_b=tb, e_bits=e_bits))
+        with np.errstate(invalid="ignore"):
+            assert_within_tolerance(got, ref, S, what)
+        zero = np.asarray(S) == 0.0
+        assert zero.any()
+        assert_bits_equal(got[zero], np.asarray(ref)[zero], "zero sums, " + what)
+
+
+@pytest.mark.parametrize("model", sorted(MODELS))
+@pytest.mark.parametrize("case", range(len(CONVS)))
+def test_wide_convolution_passes(B, model, case):
+    n, h, w, ci, co, kh, kw, s, (pt, pb, pl, pr) = CONVS[case]
+    n = max(1, n // 10)
+    d = dict(n=n, h=h, w=w, c_in=ci, c_out=co, kh=kh, kw=kw, stride_h=s, stride_w=s, pad_top=pt, pad_bottom=pb,
+             pad_left=pl, pad_right=pr)
+    oh, ow = B.conv_out_hw(d)
+    rng = np.random.default_rng(200 + case)
+    m = (8, 9, 10, 11)[case % 4]
+    x, wt = _operand(rng, (n, h, w, ci), m, 0.4), _operand(rng, (kh, kw, ci, co), m, 0.1)
+    dy = _operand(rng, (n, oh, ow, co), m, 0.4)
+    dx, dwt, ddy = (torch.from_numpy(t).cuda() for t in (x, wt, dy))
+    mid = MODELS[model]
+    for fn, ins, ref in ((B.approx_conv2d_fwd, (dx, dwt), oracle.conv2d_fwd(mid, m, d, x, wt)),
+                         (B.approx_conv2d_bwd_data, (ddy, dwt), oracle.conv2d_bwd_data(mid, m, d, dy, wt)),
+                         (B.approx_conv2d_bwd_weight, (dx, ddy), oracle.conv2d_bwd_weight(mid, m, d, x, dy))):
+        for lut, what in zip(_tables(B, model, m), ("computed", "general path")):
+            assert_within_tolerance(host(fn(d, *ins, lut, m)), *ref, "%s, %s" % (fn.__name__, what))
