@@ -706,8 +706,8 @@ __global__ __launch_bounds__(256) void reduce_splits_kernel(const float *__restr
                 float v[8];
 #pragma unroll
                 for (int k = 0; k < 8; ++k) v[k] = part[int64_t(z + k) * total + i];
-#pragma unroll
-                for (int k = 0; k < 8; ++k) s += v[k];
+                // as a tree: a shorter chain of roundings than one after another
+                s += ((v[0] + v[1]) + (v[2] + v[3])) + ((v[4] + v[5]) + (v[6] + v[7]));
             }
             for (; z < z1; ++z) s += part[int64_t(z) * total + i];
         }
@@ -1365,15 +1365,16 @@ __global__ __launch_bounds__(256) void prep_rows_wide_kernel(const uint32_t *__r
 
 // The path flags of a call on rows of 128 entries whose table kernel reads them (kTabApprox):
 // flags[1] and flags[2] (decide_paths) from the decode statistics, once the pre-pass has written
-// the entry width flags[0] and its n_tab table workgroups' words.  One workgroup.
+// the entry width flags[0] and its n_tab table workgroups' words; for a large call with the native
+// multiply, flags[1] = 3 when its matrix-core body may run.  One workgroup.
 __global__ __launch_bounds__(1024) void path_flags_kernel(const uint32_t *__restrict__ stats_a, int n_a,
                                                           const uint32_t *__restrict__ stats_b, int n_b, int narrow,
-                                                          int n_tab, int *__restrict__ flags)
+                                                          int native, int n_tab, int *__restrict__ flags)
 {
     __shared__ uint32_t red[16][4];
     uint32_t alo = 255u, ahs = 0u, blo = 255u, bhs = 0u;
     const uint32_t miss0 = int(threadIdx.x) < n_tab ? uint32_t(flags[kMissFlag + int(threadIdx.x)]) : 0u;
-    const int eb = flags[0];
+    const int eb = native ? 0 : flags[0];
     stats_fold<1024>(stats_a, n_a, alo, ahs);
     stats_fold<1024>(stats_b, n_b, blo, bhs);
     alo = wave_min(alo);
@@ -1399,9 +1400,11 @@ __global__ __launch_bounds__(1024) void path_flags_kernel(const uint32_t *__rest
             b_lo = min(b_lo, red[w][2]);
             b_hs = max(b_hs, red[w][3]);
         }
-        const int kind = add ? kMmaAdd : (exact ? kMmaExact : 0);
+        // the native multiply's matrix cores need the exact product's window
+        const int kind = native ? kMmaExact : (add ? kMmaAdd : (exact ? kMmaExact : 0));
         int path, rounded;
         decide_paths(eb, kind, false, a_lo, a_hs, b_lo, b_hs, true, narrow, path, rounded);
+        if (native) path = path == 2 + kMmaExact ? 3 : 0;
         flags[1] = path;
         flags[2] = rounded;
     }
@@ -1565,24 +1568,25 @@ inline DecFmt fmt_second(const Mode &md, const Plan &p, int m_bits)
 inline uint32_t *stats_a(char *ws, const Plan &p) { return reinterpret_cast<uint32_t *>(ws + p.off_stats); }
 inline uint32_t *stats_b(char *ws, const Plan &p) { return reinterpret_cast<uint32_t *>(ws + p.off_stats) + kStatSlots; }
 
-// A call's pre-pass jobs without the decodes' geometry: the table job (none for the native
+// The jobs of a call of `macs` products, without the decodes' geometry: the table job (none for the native
 // multiply; M <= 7 writes the rows itself, a wide table's low-bits pass is followed by
 // prep_rows_wide_kernel), the statistics and the operand formats.
-PrepJobs prep_jobs(const Mode &md, const uint32_t *lut, int mb, char *ws, const Plan &p)
+PrepJobs prep_jobs(const Mode &md, const uint32_t *lut, int mb, char *ws, const Plan &p, double macs)
 {
     PrepJobs j{};
     j.fa = fmt_first(md, mb);
     j.fb = fmt_second(md, p, mb);
-    if (md.native) return j;
+    j.t.flags = reinterpret_cast<int *>(ws + p.off_eb);
+    if (md.native && small_call(macs, 7)) return j;  // decides nothing on the device
     j.stats_a = stats_a(ws, p);
     j.stats_b = stats_b(ws, p);
+    if (md.native) return j;
     j.t.lut = lut;
     j.t.m = mb;
     j.t.vec = reinterpret_cast<uintptr_t>(lut) % 16 == 0 ? 1 : 0;
     j.t.rows = reinterpret_cast<unsigned char *>(ws + p.off_rows);
     j.t.dot_rows = reinterpret_cast<unsigned char *>(ws + p.off_dot_rows);
     j.t.hl_rows = reinterpret_cast<uint32_t *>(ws + p.off_hl_rows);
-    j.t.flags = reinterpret_cast<int *>(ws + p.off_eb);
     if (p.rl == 7) {
         j.n_tab = table_jobs(mb);
     } else {
@@ -1614,17 +1618,17 @@ int run_prepass(const PrepJobs &j, const A &a, size_t lds, int var, int narrow, 
         const int tiles = (1 << (j.t.m - 6)) * (1 << (j.t.m - 6));
         hipLaunchKernelGGL(prep_rows_wide_kernel, dim3(std::min(tiles, 2048)), dim3(256), 0, st, j.t.lut, j.t.m,
                            j.t.part, j.n_tab, j.stats_a, j.n_a, j.stats_b, j.n_b, narrow, j.t.rows, j.t.flags);
-    } else if (var == kTabApprox) {
+    } else if (var != kTabApproxSelf && j.stats_a != nullptr) {
         hipLaunchKernelGGL(path_flags_kernel, dim3(1), dim3(1024), 0, st, j.stats_a, j.n_a, j.stats_b, j.n_b, narrow,
-                           j.n_tab, j.t.flags);
+                           var == kTabNative ? 1 : 0, j.n_tab, j.t.flags);
     }
     return launch_status();
 }
 
 // The path flags the split reduction reads: only the variant that reads them has written them.
-const int *reduce_flags(const char *ws, const Plan &p, int var)
+const int *reduce_flags(const PrepJobs &j, int var)
 {
-    return var == kTabApprox ? reinterpret_cast<const int *>(ws + p.off_eb) : nullptr;
+    return var != kTabApproxSelf && j.stats_a != nullptr ? j.t.flags : nullptr;
 }
 
 // The pointers of a launch's arguments (the rest is the plan's geometry, g).
@@ -1653,6 +1657,7 @@ void set_stats(TabArgs &a, const PrepJobs &j, const Mode &md)
     a.n_a = j.n_a;
     a.n_b = j.n_b;
     a.narrow = narrow_of(md);
+    if (j.stats_a == nullptr) a.eb = nullptr;  // a small call with the native multiply: no flags
 }
 
 // Products of a convolution pass (the same for the three passes).
@@ -1875,7 +1880,8 @@ int gemm_run(const Mode &md, int trans_a, int trans_b, int64_t m, int64_t n, int
         return vec_run(md, vp, trans_a, trans_b, m, n, k, A, lda, B, ldb, C, ldc, lut, m_bits, workspace,
                        workspace_bytes, st, timer_kind);
     const int mb = plan_m(md, m_bits);
-    const Plan p = plan_gemm(m, n, k, mb);
+    Plan p = plan_gemm(m, n, k, mb);
+    if (md.native) plan_native_tiles(p);
     if (!gemm_fits(p, m, n, k)) return AMSIM_ERR_UNSUPPORTED;
     if (p.total > 0 && (!workspace || workspace_bytes < p.total)) return AMSIM_ERR_WORKSPACE;
     if (ensure_attributes() != AMSIM_OK) return AMSIM_ERR_HIP;
@@ -1886,7 +1892,7 @@ int gemm_run(const Mode &md, int trans_a, int trans_b, int64_t m, int64_t n, int
     // op(A)(i, kk): row stride / column stride in A's storage
     const int64_t a_sr = trans_a ? 1 : lda, a_sc = trans_a ? lda : 1;
     const int64_t b_sr = trans_b ? 1 : ldb, b_sc = trans_b ? ldb : 1;
-    PrepJobs j = prep_jobs(md, lut, mb, ws, p);
+    PrepJobs j = prep_jobs(md, lut, mb, ws, p, double(m) * double(n) * double(k));
     const int gx = int(std::min<int64_t>(ceil_div(p.a_ld, 64), 128)), gy = int(std::min<int64_t>(ceil_div(k, 64), 64));
     const DecT da{A, a_sr, a_sc, int(m), int(k), nullptr, int(p.a_ld), Ad, gx};
     j.n_a = gx * gy;  // <= kStatSlots
@@ -1908,7 +1914,7 @@ int gemm_run(const Mode &md, int trans_a, int trans_b, int64_t m, int64_t n, int
     if (rc != AMSIM_OK) return AMSIM_ERR_HIP;
     if (p.splits > 1) {
         launch_reduce(reinterpret_cast<const float *>(ws + p.off_part), p.splits, int(m), int(n), C, ldc, st,
-                      reduce_flags(ws, p, var), p.own_splits);
+                      reduce_flags(j, var), p.own_splits);
         if (launch_status() != AMSIM_OK) return AMSIM_ERR_HIP;
     }
     return AMSIM_OK;
@@ -1948,6 +1954,7 @@ int conv_common(const Mode &md, const amsim_conv2d *desc, int pass, const void *
     if (rc != AMSIM_OK) return rc;
     if (!in0 || !in1 || !out || (!lut && !md.native)) return AMSIM_ERR_INVALID_ARG;
     *p = plan_conv(desc, pass, plan_m(md, m_bits));
+    if (md.native) plan_native_tiles(*p);
     if (p->total > 0 && (!workspace || workspace_bytes < p->total)) return AMSIM_ERR_WORKSPACE;
     if (ensure_attributes() != AMSIM_OK) return AMSIM_ERR_HIP;
     return AMSIM_OK;
@@ -1988,7 +1995,7 @@ int fwd_core(const Mode &md, const amsim_conv2d *desc, const float *x, const flo
     uint32_t *Wd = reinterpret_cast<uint32_t *>(ws + p.off_b);
     const int64_t rows = int64_t(s.n) * s.oh * s.ow;
     float *out = p.splits > 1 ? reinterpret_cast<float *>(ws + p.off_part) : y;
-    PrepJobs j = prep_jobs(md, lut, mb, ws, p);
+    PrepJobs j = prep_jobs(md, lut, mb, ws, p, conv_macs(s));
     // w [kh][kw * ci][co] as batches kh of kw * ci rows (unfolded: padded to cu rows with +0)
     const int kwc = s.kw * s.ci, wrows = p.unfold_w ? unfolded_channels(s) : kwc;
     if (flip_w)  // batches (kh, kw) of ci rows [kh][kw][ci][co] = w[KH-1-kh][KW-1-kw][co][ci]: the last
@@ -2022,7 +2029,7 @@ int fwd_core(const Mode &md, const amsim_conv2d *desc, const float *x, const flo
     }
     if (rc != AMSIM_OK || p.splits == 1) return rc;
     launch_reduce(reinterpret_cast<const float *>(ws + p.off_part), p.splits, int(rows), s.co, y, int64_t(s.co), st,
-                  reduce_flags(ws, p, var), p.own_splits);
+                  reduce_flags(j, var), p.own_splits);
     return launch_status();
 }
 
@@ -2048,7 +2055,7 @@ int bwd_data_run(const Mode &md, const amsim_conv2d *desc, const Plan &p, const 
     uint32_t *Dyd = reinterpret_cast<uint32_t *>(ws + p.off_a);
     uint32_t *Wtd = reinterpret_cast<uint32_t *>(ws + p.off_b);
     float *out = p.splits > 1 ? reinterpret_cast<float *>(ws + p.off_part) : dx;
-    PrepJobs j = prep_jobs(md, lut, mb, ws, p);
+    PrepJobs j = prep_jobs(md, lut, mb, ws, p, conv_macs(s));
     j.z = zf;
     j.n_flag = std::min(zf.total(), 65535);
     size_t lds;
@@ -2072,7 +2079,7 @@ int bwd_data_run(const Mode &md, const amsim_conv2d *desc, const Plan &p, const 
     if (rc != AMSIM_OK) return rc;
     if (p.splits > 1) {
         launch_reduce(reinterpret_cast<const float *>(ws + p.off_part), p.splits, s.n * s.h * s.w, s.ci, dx,
-                      int64_t(s.ci), st, reduce_flags(ws, p, var), p.own_splits);
+                      int64_t(s.ci), st, reduce_flags(j, var), p.own_splits);
         if (launch_status() != AMSIM_OK) return AMSIM_ERR_HIP;
     }
     if (fixup && s.sh * s.sw > 1) {  // the taps outside each output's stride phase (dilation zeros)
@@ -2136,7 +2143,7 @@ int conv_bwd_weight_run(const Mode &md, const amsim_conv2d *desc, const float *x
     char *ws = static_cast<char *>(workspace);
     uint32_t *Xd = reinterpret_cast<uint32_t *>(ws + p.off_a);
     uint32_t *Dyd = reinterpret_cast<uint32_t *>(ws + p.off_b);
-    PrepJobs j = prep_jobs(md, lut, mb, ws, p);
+    PrepJobs j = prep_jobs(md, lut, mb, ws, p, conv_macs(s));
     // x as step-pair records inside its zero border, one padded image row per workgroup at a time
     const int64_t wc = int64_t(s.w) * s.ci;
     const int row_lds = wc <= kPairsRowWords ? 1 : 0;
@@ -2163,7 +2170,7 @@ int conv_bwd_weight_run(const Mode &md, const amsim_conv2d *desc, const float *x
     if (rc != AMSIM_OK) return AMSIM_ERR_HIP;
     if (p.splits > 1) {
         launch_reduce(reinterpret_cast<const float *>(ws + p.off_part), p.splits, R, s.co, dw, int64_t(s.co), st,
-                      reduce_flags(ws, p, var), p.own_splits);
+                      reduce_flags(j, var), p.own_splits);
         return launch_status();
     }
     return AMSIM_OK;

@@ -159,6 +159,7 @@ struct Plan {
     int64_t a_elems;      // conv: elements of the decoded first operand
     int splits;           // reduction splits
     int chunks_per_split;   // 8-step reduction chunks per split
+    int64_t own_rows, own_n, own_phases, own_q;  // bodies with tiles of their own: the result and its chunks,
     int own_c, own_splits, own_cps;  // tile width code (own_cols) and the same for the bodies with tiles of their own (plan_own_tiles)
     int64_t out_elems;      // elements of the result (partial sums hold splits of them)
     int Hp, Wp, OHp, OWp, pad_oh, pad_ow;
@@ -183,19 +184,21 @@ inline void plan_tab_split(Plan &p, int64_t taps, int64_t count)
 // tables: 256- or 128-row by own_cols-column tiles, where the gathers' tiles are up to 4096 rows by 4
 // or 8 columns), which a call takes or not only on the device: the split's partial results are reduced
 // by the count of the body that ran.  Splits only where the gathers' plan splits, so that a reduction
-// is launched either way, and at most `most` (the partial sums' room); tiles half as wide where the
-// wider ones are too few.  Priced in slabs of 4 chunks: a workgroup of 8 waves and 64 (wide tables: 128)
-// columns takes ~3 us a slab of its CU's time (44 T products/s over the chip), half as wide a tile ~60%
-// of that, CUs with fewer than 8 waves half as long again, and a split's partial sums are written and
-// read at ~4 TB/s (measured on MI355X with the gathers' splits and wide tiles, then with these: the
+// is launched either way, at least as many as the gathers' (sums no longer, so no less precise) and at
+// most `most` (the partial sums' room); tiles half as wide where the wider ones are too few.  Priced
+// in slabs of 4 chunks: a workgroup of 8 waves and 64 (wide tables: 128) columns takes ~3 us a slab of
+// its CU's time (44 T products/s over the chip), half as wide a tile ~60% of that, CUs with fewer than
+// 8 waves half as long again, and a split's partial sums are written and read at ~4 TB/s (measured on MI355X with the gathers' splits and wide tiles, then with these: the
 // ResNet-50 stem's backward-weight kernel 347 -> 288 us, a 3x3 128 -> 128 layer's at M = 11 1263 ->
 // 438 us, the GEMM 1024^3 with the exact product in a (1, 5, 10) format 206 -> 118 us).
-inline void plan_own_tiles(Plan &p, int64_t rows, int64_t cols, int64_t phases, int64_t taps, int64_t count,
-                           int64_t most)
+inline void plan_own_tiles(Plan &p, int64_t rows, int64_t cols, int64_t phases, int64_t q, bool wide, int64_t most)
 {
+    p.own_rows = rows;
+    p.own_n = cols;
+    p.own_phases = phases;
+    p.own_q = q;
     p.own_c = 0;
-    const int64_t q = taps * ceil_div(count, p.chunk);
-    const int nw = p.tile.nw, wide = p.rl > 7 ? 1 : 0;
+    const int nw = p.tile.nw;
     double best = 0.0;
     for (int half = 0; half < 2; ++half) {
         const int c = (wide ? 8 : 4) >> half;
@@ -203,8 +206,10 @@ inline void plan_own_tiles(Plan &p, int64_t rows, int64_t cols, int64_t phases, 
         const int64_t base = ceil_div(rows, 32 * nw) * ceil_div(cols, own_cols(c)) * phases;
         const double slab_us = (nw == 8 ? 3.0 : 1.5) * (half ? 0.6 : 1.0);
         auto consider = [&](int64_t s) {
-            s = std::max<int64_t>(1, std::min(std::min(s, most), ceil_div(q, 4)));
-            const int64_t cps = s == 1 ? std::max<int64_t>(1, q) : round_up(ceil_div(q, s), 4), s_eff = ceil_div(std::max<int64_t>(1, q), cps);
+            s = std::min(s, most);
+            int64_t cps = std::max<int64_t>(1, ceil_div(q, std::max<int64_t>(1, s)));
+            if (p.splits > 1) cps = std::min<int64_t>(round_up(cps, 4), p.chunks_per_split);
+            const int64_t s_eff = std::max<int64_t>(1, ceil_div(q, cps));
             const double per_cu = double(ceil_div(base * s_eff, 256));
             double us = per_cu * double(ceil_div(cps, 4)) * slab_us * (per_cu * nw < 8.0 ? 1.5 : 1.0);
             if (p.splits > 1) us += double(s_eff) * double(p.out_elems) * 8.0 / 4.0e6;
@@ -269,7 +274,7 @@ inline Plan plan_gemm(int64_t m, int64_t n, int64_t k, int m_bits)
     p.off_b = o;
     o += align_up(size_t(k) * p.b_ld * 4);
     p.out_elems = m * n;
-    plan_own_tiles(p, m, n, 1, 1, k, p.splits);
+    plan_own_tiles(p, m, n, 1, ceil_div(k, p.chunk), p.rl > 7, p.splits);
     p.off_part = o;
     if (p.splits > 1) o += align_up(size_t(p.splits) * m * n * 4);
     p.total = o;
@@ -426,6 +431,13 @@ inline bool bwd_data_unfolds(const amsim_conv2d *d)
     return check_conv(&v, AMSIM_CONV_BWD_DATA) == AMSIM_OK && int64_t(v.n) * v.h * v.w * v.c_in < (int64_t(1) << 29);
 }
 
+// The native multiply's matrix-core body has the wide tables' tile widths, in the same workspace.
+inline void plan_native_tiles(Plan &p)
+{
+    const int64_t most = std::max(p.splits, p.own_splits);
+    plan_own_tiles(p, p.own_rows, p.own_n, p.own_phases, p.own_q, true, most);
+}
+
 // Room for partial sums of the own-tile bodies: up to 64 MiB, or what the gathers' splits take.
 inline int64_t own_most(const Plan &p)
 {
@@ -463,7 +475,8 @@ inline Plan plan_conv(const amsim_conv2d *d, int pass, int m_bits)
         p.b_ld = round_up(s.co, tab_cols(p.tile));
         p.a_elems = int64_t(s.n) * p.Hp * p.Wp * ((p.rec_c + 1) / 2) * 3;  // zero-bordered x as step-pair records
         p.out_elems = npix_out * s.co;
-        plan_own_tiles(p, npix_out, s.co, 1, int64_t(v.kh) * v.kw * p.csplit, v.ci / p.csplit, own_most(p));
+        plan_own_tiles(p, npix_out, s.co, 1, int64_t(v.kh) * v.kw * p.csplit * ceil_div(v.ci / p.csplit, p.chunk), p.rl > 7,
+                       own_most(p));
         p.off_a = o;
         o += align_up(size_t(p.a_elems) * 4);
         p.off_b = o;  // decoded w [kh*kw*ci][COp] (unfolded: [kh][cu][COp])
@@ -484,8 +497,9 @@ inline Plan plan_conv(const amsim_conv2d *d, int pass, int m_bits)
         p.b_ld = round_up(s.ci, tab_cols(p.tile));
         p.a_elems = int64_t(s.n) * p.OHp * p.OWp * ((p.rec_c + 1) / 2) * 3;  // zero-padded dy as step-pair records
         p.out_elems = npix_in * s.ci;
-        plan_own_tiles(p, rows, s.ci, int64_t(s.sh) * s.sw, ceil_div(s.kh, s.sh) * ceil_div(s.kw, s.sw) * p.csplit,
-                        s.co / p.csplit, p.splits);
+        plan_own_tiles(p, rows, s.ci, int64_t(s.sh) * s.sw,
+                       ceil_div(s.kh, s.sh) * ceil_div(s.kw, s.sw) * p.csplit * ceil_div(s.co / p.csplit, p.chunk),
+                       p.rl > 7, p.splits);
         p.off_a = o;
         o += align_up(size_t(p.a_elems) * 4);
         p.off_b = o;  // decoded w^T [kh][kw][co][CIp]
@@ -500,7 +514,7 @@ inline Plan plan_conv(const amsim_conv2d *d, int pass, int m_bits)
         p.b_ld = round_up(s.co, tab_cols(p.tile));
         p.a_elems = int64_t(s.n) * p.Hp * p.Wp * s.ci * 3;
         p.out_elems = R * s.co;
-        plan_own_tiles(p, R, s.co, 1, int64_t(s.n) * s.oh, s.ow, own_most(p));
+        plan_own_tiles(p, R, s.co, 1, int64_t(s.n) * s.oh * ceil_div(s.ow, p.chunk), p.rl > 7, own_most(p));
         p.off_a = o;  // zero-bordered x as step-pair records, one per element
         o += align_up(size_t(p.a_elems) * 4);
         p.off_b = o;  // decoded dy [n*oh*ow][COp]

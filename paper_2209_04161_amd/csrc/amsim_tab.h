@@ -945,6 +945,188 @@ __device__ __forceinline__ void tab_body_native(const TabArgs &a)
     }
 }
 
+// The same on the FP32 matrix cores, for large calls whose operands keep every product normal and finite
+// (path 3 of the flags, from the decode statistics; then denormal operands, read as zero, are the
+// only ones to flush).  A workgroup of NW waves computes 32 NW rows by 16 TN columns: TN = 8 (waves of
+// 64 x 64) or 4 (waves of 32 x 64), in 32 x 32 blocks of v_mfma_f32_32x32x2_f32.  Both operands go
+// through LDS in double-buffered slabs of 16 steps, [chunk of 8 steps][half][row or column][4 steps]:
+// a lane reads 4 of a chunk's steps at once, the lanes of the instruction's first step its first half,
+// those of the second step the second half.
+// What bounds it: the matrix cores (157 TFLOP/s) where the rows' records arrive in time.  Measured on
+// MI355X, the scalar kernels and these: ResNet 3x3 forward 362 -> 124 us (78 TFLOP/s), backward weight
+// 485 -> 142 us; the three passes with their pre-passes 1246 -> 446 us.
+typedef float f32x16_t __attribute__((ext_vector_type(16)));
+typedef float f32x4n_t __attribute__((ext_vector_type(4)));
+constexpr int kNatSteps = 16;
+constexpr int nat_buf_bytes(int nw, int tn) { return kNatSteps * (32 * nw + 16 * tn) * 4; }
+
+template <int OP, int NW, int TN>
+__device__ __forceinline__ void tab_body_native_mma(const TabArgs &a0)
+{
+    constexpr int NT = 64 * NW, KS = kNatSteps;
+    constexpr int ROWS = 32 * NW, COLS = 16 * TN;
+    constexpr int RB = TN == 8 ? 2 : 1, CB = 2;   // 32 x 32 blocks of a wave
+    constexpr int WC = TN == 8 ? 2 : 1;           // waves along columns
+    constexpr int ABYTES = KS * ROWS * 4, BUF = nat_buf_bytes(NW, TN);
+    constexpr int BG = KS * COLS / 4;             // staged groups of 4 steps of the second operand
+    constexpr int BPT = (BG + NT - 1) / NT;
+    TabArgs a = a0;
+    int tx, ty;
+    if (!own_tile(a, (a.R + ROWS - 1) / ROWS, (a.N + COLS - 1) / COLS, tx, ty)) return;
+    const int R = tab_rows<OP>(a);
+    if (tx * ROWS >= R) return;  // uniform over the workgroup
+    const int lane = threadIdx.x & 63, n = lane & 31, hk = lane >> 5;
+    const int wave = wave_id();
+    const int roww = tx * ROWS, colw = ty * COLS;
+    const int wr0 = (wave / WC) * (32 * RB), wc0 = (wave % WC) * (32 * CB);
+    const bool live = roww + wr0 < R && colw + wc0 < a.N;  // wave-uniform
+
+    const int count = tab_count<OP>(a), ch = a.chunk;  // ch = 8 steps: half a slab
+    const int cpt = (count + ch - 1) / ch;
+    const int q_total = tab_taps<OP>(a) * cpt;
+    const int q0 = tab_split(a) * a.chunks_per_split, q1 = min(q_total, q0 + a.chunks_per_split);
+
+    const int srow = int(threadIdx.x) % ROWS, sc = __builtin_amdgcn_readfirstlane(int(threadIdx.x) / ROWS);
+    const __amdgpu_buffer_rsrc_t arec =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t *>(a.A), 0, int(a.a_bytes), 0x00020000);
+    const uint32_t aoff = uint32_t(roww + srow < R ? tab_row_rec<OP>(a, roww + srow) : 0) * kPairRecordBytes;
+    u32x3 sa[4];
+    f32x4n_t sb[BPT];
+    auto fetch = [&](int qs) __attribute__((always_inline)) {
+        {
+            const int q = min(qs + sc, q1 - 1);  // past the end: finite values, against zeros of b
+            const int tap = OP == OP_GEMM ? 0 : q / cpt;
+            const TabTap tp = tab_tap_raw<OP>(a, tap);
+            const int c0 = (q - tap * cpt) * ch;
+#pragma unroll
+            for (int p = 0; p < 4; ++p) {
+                const uint32_t so = __builtin_amdgcn_readfirstlane(
+                    uint32_t(tp.pbase + min(c0 / 2 + p, (count - 1) / 2) * tp.ustride) * kPairRecordBytes);
+                sa[p] = __builtin_amdgcn_raw_buffer_load_b96(arec, aoff, so, 0);
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < BPT; ++i) {
+            const int u = int(threadIdx.x) + i * NT, col = colw + u % COLS, g = u / COLS, q = qs + g / 2;
+            sb[i] = f32x4n_t{0.0f, 0.0f, 0.0f, 0.0f};
+            if (u < BG && q < q1 && col < a.Np) {
+                const int tap = OP == OP_GEMM ? 0 : q / cpt;
+                const int j = (q - tap * cpt) * ch + (g % 2) * 4, row = tab_tap_raw<OP>(a, tap).bbase + j;
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if (j + e < count) sb[i][e] = __uint_as_float(Bd_word(a, row + e, col));
+            }
+        }
+    };
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    auto commit = [&](int buf) __attribute__((always_inline)) {
+        unsigned char *ab = smem + buf * BUF, *bb = ab + ABYTES;
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            f32x4n_t v;
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                v[e] = __builtin_canonicalizef(__uint_as_float(e % 2 ? sa[2 * h + e / 2].z : sa[2 * h + e / 2].x));
+            *reinterpret_cast<f32x4n_t *>(ab + ((sc * 2 + h) * ROWS + srow) * 16) = v;
+        }
+#pragma unroll
+        for (int i = 0; i < BPT; ++i) {
+            const int u = int(threadIdx.x) + i * NT;
+            if (BG % NT != 0 && u >= BG) break;
+            f32x4n_t v;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[e] = __builtin_canonicalizef(sb[i][e]);
+            *reinterpret_cast<f32x4n_t *>(bb + u * 16) = v;
+        }
+    };
+    f32x16_t acc[RB][CB];
+#pragma unroll
+    for (int r = 0; r < RB; ++r)
+#pragma unroll
+        for (int c = 0; c < CB; ++c)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) acc[r][c][e] = -0.0f;
+    int buf = 0;
+    bool have = false;
+    for (int qs = q0;; qs += KS / 8) {  // slab qs is staged while the one before it is computed
+        const bool more = qs < q1;
+        if (more) fetch(qs);
+        if (live && have) {
+            const unsigned char *ab = smem + (buf ^ 1) * BUF + (hk * ROWS + wr0 + n) * 16;
+            const unsigned char *bb = smem + (buf ^ 1) * BUF + ABYTES + (hk * COLS + wc0 + n) * 16;
+#pragma unroll
+            for (int c8 = 0; c8 < KS / 8; ++c8) {
+                f32x4n_t x[RB], y[CB];
+#pragma unroll
+                for (int r = 0; r < RB; ++r)
+                    x[r] = *reinterpret_cast<const f32x4n_t *>(ab + (c8 * 2 * ROWS + r * 32) * 16);
+#pragma unroll
+                for (int c = 0; c < CB; ++c)
+                    y[c] = *reinterpret_cast<const f32x4n_t *>(bb + (c8 * 2 * COLS + c * 32) * 16);
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+#pragma unroll
+                    for (int r = 0; r < RB; ++r)
+#pragma unroll
+                        for (int c = 0; c < CB; ++c)
+                            acc[r][c] = __builtin_amdgcn_mfma_f32_32x32x2f32(x[r][e], y[c][e], acc[r][c], 0, 0, 0);
+            }
+        }
+        if (!more) break;
+        commit(buf);
+        __syncthreads();
+        buf ^= 1;
+        have = true;
+    }
+    if (!live) return;
+
+    // Lane (n, hk) holds, of a block, column n and rows 8 (i / 4) + 4 hk + i % 4.  Signs of exactly-zero
+    // sums: -0 when every product of the split's range is -0, else +0.
+    float *outp = a.out + int64_t(tab_split(a)) * a.out_elems;
+#pragma unroll
+    for (int c = 0; c < CB; ++c) {
+        const int col = colw + wc0 + c * 32 + n;
+        const bool colok = col < a.N;
+#pragma unroll
+        for (int r = 0; r < RB; ++r) {
+            const int row0 = roww + wr0 + r * 32 + 4 * hk;
+            uint32_t pending = 0u;
+#pragma unroll
+            for (int i = 0; i < 16; ++i)
+                if (colok && row0 + 8 * (i / 4) + i % 4 < R && acc[r][c][i] == 0.0f) pending |= 1u << i;
+            const uint32_t zero = pending;
+            if (__builtin_amdgcn_ballot_w64(pending != 0u) != 0u) {
+                uint32_t ro[16];
+#pragma unroll
+                for (int i = 0; i < 16; ++i) {
+                    const int row = row0 + 8 * (i / 4) + i % 4;
+                    ro[i] = row < R ? uint32_t(tab_row_rec<OP>(a, row)) * kPairRecordBytes : 0u;
+                }
+                for (int p = q0 * ch; p < q1 * ch && __builtin_amdgcn_ballot_w64(pending != 0u) != 0u; ++p) {
+                    const int tap = p / (cpt * ch), j = p - tap * (cpt * ch);
+                    if (j >= count) continue;  // a chunk's padding steps
+                    const TabTap tp = tab_tap<OP>(a, tap);
+                    const uint32_t so = __builtin_amdgcn_readfirstlane(a_step_offset<OP>(tp, j));
+                    const float pb = colok ? __uint_as_float(Bd_word(a, tp.bbase + j, col)) : 0.0f;
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) {
+                        const u32x2 d = __builtin_amdgcn_raw_buffer_load_b64(arec, ro[i], so + (j & 1) * 4u, 0);
+                        if (__float_as_uint(__uint_as_float((j & 1) ? d.y : d.x) * pb) != 0x80000000u)
+                            pending &= ~(1u << i);
+                    }
+                }
+            }
+#pragma unroll
+            for (int i = 0; i < 16; ++i) {
+                const int row = row0 + 8 * (i / 4) + i % 4;
+                float v = acc[r][c][i];
+                if ((zero >> i) & 1u) v = ((pending >> i) & 1u) ? -0.0f : 0.0f;
+                if (colok && row < R) outp[tab_row_out<OP>(a, row) + col] = __builtin_canonicalizef(v);
+            }
+        }
+    }
+}
+
 // ---------------------------------------------------------- bf16 pair path (1-byte tables)
 // When every table entry fits 8 bits (its low 16 mantissa bits are zero) a table value v is a
 // bfloat16, and so are v * pb (the second operand's sign and exponent added to v's bits) and pa.
@@ -2161,6 +2343,13 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(4, 4)))
 {
     TabArgs a = args;
     if constexpr (VAR == kTabNative) {
+        if (a.eb != nullptr && __builtin_amdgcn_readfirstlane(a.eb[1]) == 3) {  // a large call
+            if (a.own_c == 8)
+                tab_body_native_mma<OP, NW, 8>(a);
+            else
+                tab_body_native_mma<OP, NW, 4>(a);
+            return;
+        }
         if (tab_tile_id(a)) tab_body_native<OP, TM, TN, WR, NW>(a);
         return;
     }
@@ -2245,7 +2434,8 @@ constexpr size_t tab_exact_lds_bytes(int tnw, int rl, int eb)
 
 constexpr size_t tab_native_lds_bytes(int tn, int wr, int nw)
 {
-    return size_t(2) * kNativeSlabSteps * tn * (nw / wr) * 4;
+    const size_t v = size_t(2) * kNativeSlabSteps * tn * (nw / wr) * 4, mma = size_t(2) * nat_buf_bytes(nw, 8);
+    return v > mma ? v : mma;
 }
 
 constexpr size_t tab_lds_bytes(int tn, int wr, int nw, int rl)

@@ -69,10 +69,10 @@ hipError_t tab_launch_of(const Tile &t, int rl, int var, const TabArgs &args, di
     a.gx = int(tiles.x);
     a.gy = int(tiles.y);
     a.gz = int(tiles.z);
-    // the bodies of additive and exact-product tables tile the result their own way: workgroups for
+    // the bodies of additive and exact-product tables and the native multiply's matrix-core body tile the result their own way: workgroups for
     // whichever tiles are more
     int64_t blocks = int64_t(tiles.x) * tiles.y * tiles.z;
-    if (var == kTabApprox) {
+    if (var == kTabApprox || (var == kTabNative && a.eb != nullptr)) {
         const int rows = 32 * t.nw, cols = own_cols(a.own_c);
         const int64_t own = (int64_t(a.R) + rows - 1) / rows * ((int64_t(a.N) + cols - 1) / cols) *
                             (int64_t(tiles.z) / a.splits * a.own_splits);

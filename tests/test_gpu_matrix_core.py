@@ -183,3 +183,50 @@ def test_wide_convolution_passes(B, model, case):
                          (B.approx_conv2d_bwd_weight, (dx, ddy), oracle.conv2d_bwd_weight(mid, m, d, x, dy))):
         for lut, what in zip(_tables(B, model, m), ("computed", "general path")):
             assert_within_tolerance(host(fn(d, *ins, lut, m)), *ref, "%s, %s" % (fn.__name__, what))
+
+
+@pytest.mark.parametrize("inside", [True, False])
+@pytest.mark.parametrize("case", range(len(GEMMS)))
+def test_native_multiply_gemm(B, case, inside):
+    """Large calls with the native multiply: the matrix cores inside the operand window, the fma kernels
+    with an operand so large that some product could overflow (none does); denormal operands, read as
+    zero, on either."""
+    m, n, k, ta, tb = GEMMS[case]
+    rng = np.random.default_rng(300 + case)
+    a, b = _operand(rng, (m, k), 7, 0.3), _operand(rng, (k, n), 7, 0.2)
+    a[m // 2] = -0.0
+    b[:, n // 2] = np.where(rng.random(k) < 0.5, 0.0, -0.0)
+    a[0] = (a[0].view(np.uint32) & np.uint32(0x807FFFFF)).view(np.float32)
+    if not inside:
+        a[m - 1, 0] = np.float32(2.0) ** 120
+        b[0] = np.float32(2.0) ** -27
+    da = torch.from_numpy(np.ascontiguousarray(a.T if ta else a)).cuda()
+    db = torch.from_numpy(np.ascontiguousarray(b.T if tb else b)).cuda()
+    got = host(B.approx_gemm_ex(da, db, None, 7, trans_a=ta, trans_b=tb, multiply="native"))
+    cols = np.unique(np.r_[0, n // 2, n - 1, rng.integers(0, n, 40)])
+    idx = (np.arange(m)[:, None] * n + cols).reshape(-1)
+    ref, S = oracle.gemm(MODELS["mitchell"], 7, a, b, idx=idx, native=True)
+    got = got.reshape(-1)[idx]
+    with np.errstate(invalid="ignore"):
+        assert_within_tolerance(got, ref, S, "native GEMM")
+    zero = np.asarray(S) == 0.0
+    assert zero.any()
+    assert_bits_equal(got[zero], np.asarray(ref)[zero], "zero sums")
+
+
+@pytest.mark.parametrize("case", range(len(CONVS)))
+def test_native_multiply_convolutions(B, case):
+    n, h, w, ci, co, kh, kw, s, (pt, pb, pl, pr) = CONVS[case]
+    d = dict(n=n, h=h, w=w, c_in=ci, c_out=co, kh=kh, kw=kw, stride_h=s, stride_w=s, pad_top=pt, pad_bottom=pb,
+             pad_left=pl, pad_right=pr)
+    oh, ow = B.conv_out_hw(d)
+    rng = np.random.default_rng(400 + case)
+    x, wt = _operand(rng, (n, h, w, ci), 7, 0.4), _operand(rng, (kh, kw, ci, co), 7, 0.1)
+    dy = _operand(rng, (n, oh, ow, co), 7, 0.4)
+    dx, dwt, ddy = (torch.from_numpy(t).cuda() for t in (x, wt, dy))
+    mid = MODELS["mitchell"]
+    for fn, ins, ref in (
+            (B.approx_conv2d_fwd_ex, (dx, dwt), oracle.conv2d_fwd(mid, 7, d, x, wt, native=True)),
+            (B.approx_conv2d_bwd_data_ex, (ddy, dwt), oracle.conv2d_bwd_data(mid, 7, d, dy, wt, native=True)),
+            (B.approx_conv2d_bwd_weight_ex, (dx, ddy), oracle.conv2d_bwd_weight(mid, 7, d, x, dy, native=True))):
+        assert_within_tolerance(host(fn(d, *ins, None, 7, multiply="native")), *ref, fn.__name__)
