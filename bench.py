@@ -204,7 +204,7 @@ def main():
                 "traffic_source": "not measured in this run: HBM bytes per launch from the committed rocprofv3 "
                                   "FETCH_SIZE/WRITE_SIZE summary profiles/gemm_4096_m7_traffic.txt, used only while "
                                   "its kernel_source_sha256 matches the kernel sources (else null)",
-                "kernel": "tab_kernel<OP_GEMM, 4, 8, 8, 8, 7, kTabApprox> (approx_gemm 4096^3, Mitchell M=7, bf16 pair path)"}
+                "kernel": "tab_kernel<OP_GEMM, 4, 8, 8, 8, 7, kTabApprox> (approx_gemm 4096^3, Mitchell M=7, additive table on the matrix cores)"}
 
     out = {
         "metric": METRIC,
