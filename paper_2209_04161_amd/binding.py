@@ -255,7 +255,7 @@ def _check_workspace(ws, nbytes, device):
         raise ValueError("workspace holds %d bytes, the call needs %d" % (ws.numel(), nbytes))
 
 
-@functools.lru_cache(maxsize=1024)
+@functools.lru_cache(maxsize=1024, typed=True)
 def _gemm_ws_bytes(trans_a, trans_b, m, n, k, m_bits) -> int:
     b = ctypes.c_size_t(0)
     _check(lib().amsim_gemm_workspace_size(trans_a, trans_b, m, n, k, m_bits, ctypes.byref(b)),
@@ -387,7 +387,7 @@ def _conv_shapes(desc):
     return x, w, y
 
 
-@functools.lru_cache(maxsize=1024)
+@functools.lru_cache(maxsize=1024, typed=True)
 def _conv_plan(values, pass_id):
     """Of a descriptor (its fields' values) and pass: the C struct (read-only from here on), the shapes
     of x, w and y, and a dict for the workspace bytes per m_bits."""
