@@ -1138,12 +1138,14 @@ __global__ void cast_kernel(int64_t n, const float *__restrict__ x, float *__res
 // bf16 path stages them (byte 4 * (ka % 32) + ka / 32 of row kb), with 2-byte entries hl_rows the
 // entries split into bf16 halves for the hi/lo path.  Every workgroup ORs the whole table for eb
 // (a few tens of KiB, read from L2 after the first) and writes the rows kb of its share;
-// workgroup 0 also writes flags[0] = eb and the zero rows.  Workgroup b writes flags[kMissFlag + b],
-// the kinds of table that its share of the entries rules out (table_misses); path_flags_kernel ORs them.
+// workgroup 0 also writes flags[0] = eb and the zero rows.  Where path_flags_kernel follows (kinds),
+// workgroup b writes flags[kMissFlag + b], the kinds of table that its share of the entries rules out
+// (table_misses), for it to OR.
 struct TablePrep {
     const uint32_t *lut;
     int m;
     int vec;               // lut 16-byte aligned
+    int kinds;             // M <= 7: check the table's kind
     unsigned char *rows, *dot_rows;
     uint32_t *hl_rows;
     int *flags;
@@ -1151,7 +1153,12 @@ struct TablePrep {
 };
 
 // Workgroups of the table job for M <= 7: rows of 8 entries kb each.
-inline int table_jobs(int m) { return std::max(1, std::min(16, (1 << m) / 8)); }
+constexpr int table_jobs(int m) { return std::max(1, std::min(16, (1 << m) / 8)); }
+// Entries per thread of the job's workgroups, the most over M <= 7.
+constexpr int kKindShare = 4;
+static_assert(table_jobs(7) * 256 * kKindShare >= 1 << 14 && table_jobs(6) * 256 * kKindShare >= 1 << 12 &&
+                  table_jobs(5) * 256 * kKindShare >= 1 << 10,
+              "the share covers the table");
 
 __device__ __forceinline__ uint32_t block_or(uint32_t v, uint32_t *s4)
 {
@@ -1180,6 +1187,15 @@ __device__ __forceinline__ void prep_table_body(const TablePrep &t, int bid, int
     __shared__ uint32_t s_low[4];
     const uint32_t *__restrict__ lut = t.lut;
     const int n = 1 << t.m, total = n * n;
+    // the workgroup's share of the entries for the kind check, at most kKindShare a thread (table_jobs),
+    // loaded ahead of the whole table's so that no wait of its own comes after it
+    uint32_t share[kKindShare] = {};
+    if (t.kinds)
+#pragma unroll
+        for (int k = 0; k < kKindShare; ++k) {
+            const int i = (k * nblk + bid) * 256 + int(threadIdx.x);
+            if (i < total) share[k] = lut[i];
+        }
     uint32_t low = 0u;
     if (t.vec) {
 #pragma unroll 4
@@ -1192,15 +1208,18 @@ __device__ __forceinline__ void prep_table_body(const TablePrep &t, int bid, int
 #pragma unroll 4
         for (int i = threadIdx.x; i < total; i += 256) low |= lut[i];
     }
-    // the table's kind: each workgroup checks its share of the entries
     low &= 0xFFFFu;
-    if (t.m >= 3)
-        for (int i = bid * 256 + int(threadIdx.x); i < total; i += nblk * 256) low |= table_misses(lut[i], i, t.m);
+    if (t.kinds && t.m >= 3)
+#pragma unroll
+        for (int k = 0; k < kKindShare; ++k) {
+            const int i = (k * nblk + bid) * 256 + int(threadIdx.x);
+            if (i < total) low |= table_misses(share[k], i, t.m);
+        }
     const uint32_t lb = block_or(low, s_low);
     const int eb = (lb & 0xFFFFu) == 0u ? 1 : ((lb & 0xFFu) == 0u ? 2 : 4);
     const bool lead = bid == 0;
     if (lead && threadIdx.x == 0) t.flags[0] = eb;
-    if (threadIdx.x == 0) t.flags[kMissFlag + bid] = int(t.m < 3 ? kMissAdd | kMissExact : lb & (kMissAdd | kMissExact));
+    if (t.kinds && threadIdx.x == 0) t.flags[kMissFlag + bid] = int(t.m < 3 ? kMissAdd | kMissExact : lb & (kMissAdd | kMissExact));
     const int per = (n + nblk - 1) / nblk, kb0 = bid * per, nk = max(0, min(n, kb0 + per) - kb0);
     unsigned char *__restrict__ dst = t.rows;
     // rows: thread -> (kb, group of 4 entries), consecutive threads along kb
@@ -1598,6 +1617,7 @@ PrepJobs prep_jobs(const Mode &md, const uint32_t *lut, int mb, char *ws, const 
     j.t.hl_rows = reinterpret_cast<uint32_t *>(ws + p.off_hl_rows);
     if (p.rl == 7) {
         j.n_tab = table_jobs(mb);
+        j.t.kinds = small_call(macs, p.rl) ? 0 : 1;  // kTabApproxSelf has no body for them
     } else {
         j.wide = 1;
         j.t.part = reinterpret_cast<uint32_t *>(ws + p.off_wpart);
