@@ -1138,7 +1138,7 @@ __global__ void cast_kernel(int64_t n, const float *__restrict__ x, float *__res
 // bf16 path stages them (byte 4 * (ka % 32) + ka / 32 of row kb), with 2-byte entries hl_rows the
 // entries split into bf16 halves for the hi/lo path.  Every workgroup ORs the whole table for eb
 // (a few tens of KiB, read from L2 after the first) and writes the rows kb of its share;
-// workgroup 0 also writes flags[0] = eb and the zero rows.  Where path_flags_kernel follows (kinds),
+// workgroup 0 also writes flags[0] = eb and the zero rows.  Where own_kernel follows (kinds),
 // workgroup b writes flags[kMissFlag + b], the kinds of table that its share of the entries rules out
 // (table_misses), for it to OR.
 struct TablePrep {
@@ -1172,8 +1172,6 @@ __device__ __forceinline__ uint32_t block_or(uint32_t v, uint32_t *s4)
 // Whether entry i = (ka << m) + kb is not the additive table's, (ka + kb) << (23 - m) (kMissAdd), or
 // not the exact product's of 1.ka and 1.kb (kMissExact), for 3 <= m <= 11: the kinds kMmaAdd and
 // kMmaExact, Mitchell's multiplier and the exact truncated product.
-constexpr uint32_t kMissAdd = 0x80000000u, kMissExact = 0x40000000u, kMissSum = 0x20000000u;
-constexpr int kMissFlag = 16;  // of the flags' 64 words, one per table workgroup (table_jobs) from here
 __device__ __forceinline__ uint32_t table_misses(uint32_t entry, int i, int m)
 {
     const uint32_t n = 1u << m, ka = uint32_t(i) >> m, kb = uint32_t(i) & (n - 1u), e = entry & 0x00FFFFFFu;
@@ -1317,92 +1315,16 @@ __device__ __forceinline__ void lut_low_bits_body(const TablePrep &t, int bid, i
     if (threadIdx.x == 0) t.part[bid] = r;
 }
 
-// Second launch for wide tables: the entry width from the nparts partial words, then the
-// transposed rows -- row kb (2^m entries of eb bytes) holds entry (ka, kb) at byte ka * eb --
-// through 64 x 64 LDS tiles (loads along kb, stores along ka).  Workgroup 0 writes flags[0] = eb,
-// flags[1], an arithmetic body's path or 0 (no bf16 path for wide rows), flags[2], the exact path's product form, from
-// the decode statistics (n_a and n_b words; null for the native multiply), and flags[3] = 1 when
-// the table is sum-indexed.
-__global__ __launch_bounds__(256) void prep_rows_wide_kernel(const uint32_t *__restrict__ lut, int m,
-                                                             const uint32_t *__restrict__ part, int nparts,
-                                                             const uint32_t *__restrict__ stats_a, int n_a,
-                                                             const uint32_t *__restrict__ stats_b, int n_b,
-                                                             int narrow, unsigned char *__restrict__ dst,
-                                                             int *__restrict__ flags)
-{
-    __shared__ uint32_t tile[64][65];
-    __shared__ uint32_t s_low[4], s_alo[4], s_blo[4], s_ahs[4], s_bhs[4];
-    uint32_t low = 0u;
-    for (int i = threadIdx.x; i < nparts; i += 256) low |= part[i];
-    const uint32_t lb = block_or(low, s_low);
-    const int eb = (lb & 0xFFFFu) == 0u ? 1 : ((lb & 0xFFu) == 0u ? 2 : 4);
-    if (blockIdx.x == 0) {  // uniform
-        uint32_t alo = 255u, ahs = 0u, blo = 255u, bhs = 0u;
-        const bool have = stats_a != nullptr;
-        if (have) {
-            stats_fold<256>(stats_a, n_a, alo, ahs);
-            stats_fold<256>(stats_b, n_b, blo, bhs);
-        }
-        alo = wave_min(alo);
-        blo = wave_min(blo);
-        ahs = wave_max(ahs);
-        bhs = wave_max(bhs);
-        if ((threadIdx.x & 63) == 0) {
-            s_alo[threadIdx.x >> 6] = alo;
-            s_blo[threadIdx.x >> 6] = blo;
-            s_ahs[threadIdx.x >> 6] = ahs;
-            s_bhs[threadIdx.x >> 6] = bhs;
-        }
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            const uint32_t a_lo = min(min(s_alo[0], s_alo[1]), min(s_alo[2], s_alo[3]));
-            const uint32_t b_lo = min(min(s_blo[0], s_blo[1]), min(s_blo[2], s_blo[3]));
-            const uint32_t a_hs = max(max(s_ahs[0], s_ahs[1]), max(s_ahs[2], s_ahs[3]));
-            const uint32_t b_hs = max(max(s_bhs[0], s_bhs[1]), max(s_bhs[2], s_bhs[3]));
-            int path, rounded;
-            const int kind = (lb & kMissAdd) == 0u ? kMmaAdd : ((lb & kMissExact) == 0u ? kMmaExact : 0);
-            decide_paths(eb, kind, true, a_lo, a_hs, b_lo, b_hs, have, narrow, path, rounded);
-            flags[0] = eb;
-            flags[1] = path;
-            flags[2] = rounded;
-            flags[3] = (lb & kMissSum) == 0u ? 1 : 0;
-        }
-    }
-    if ((lb & kMissAdd) == 0u || (lb & kMissExact) == 0u) return;  // computed, no row is read (uniform)
-    const int n = 1 << m, tiles_1d = n / 64;
-    const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
-    for (int t = blockIdx.x; t < tiles_1d * tiles_1d; t += gridDim.x) {
-        const int ka0 = (t / tiles_1d) * 64, kb0 = (t % tiles_1d) * 64;
-        // a sum-indexed table's entries are read at kb = 0 and at ka = 2^m - 1 only
-        if ((lb & kMissSum) == 0u && kb0 != 0 && ka0 != n - 64) continue;
-        for (int i = ty; i < 64; i += 4) tile[i][tx] = lut[size_t(ka0 + i) * n + kb0 + tx];  // [ka][kb]
-        __syncthreads();
-        for (int i = ty; i < 64; i += 4) {
-            const uint32_t e = tile[tx][i] & 0x00FFFFFFu;  // entry (ka0 + tx, kb0 + i)
-            unsigned char *row = dst + size_t(kb0 + i) * n * eb;
-            if (eb == 1)
-                row[ka0 + tx] = static_cast<unsigned char>(e >> 16);
-            else if (eb == 2)
-                reinterpret_cast<uint16_t *>(row)[ka0 + tx] = static_cast<uint16_t>(e >> 8);
-            else
-                reinterpret_cast<uint32_t *>(row)[ka0 + tx] = e + 0x3F800000u;
-        }
-        __syncthreads();
-    }
-}
-
-// The path flags of a call on rows of 128 entries whose table kernel reads them (kTabApprox):
-// flags[1] and flags[2] (decide_paths) from the decode statistics, once the pre-pass has written
-// the entry width flags[0] and its n_tab table workgroups' words; for a large call with the native
-// multiply, flags[1] = 3 when its matrix-core body may run.  One workgroup.
+// The path flags of a call on rows of 128 entries that own_kernel does not decide (it has no body for
+// the call) and that is no small one: flags[1] and flags[2] (decide_paths) from the decode statistics, once
+// the pre-pass has written the entry width flags[0].  One workgroup.
 __global__ __launch_bounds__(1024) void path_flags_kernel(const uint32_t *__restrict__ stats_a, int n_a,
                                                           const uint32_t *__restrict__ stats_b, int n_b, int narrow,
-                                                          int native, int n_tab, int *__restrict__ flags)
+                                                          int *__restrict__ flags)
 {
     __shared__ uint32_t red[16][4];
     uint32_t alo = 255u, ahs = 0u, blo = 255u, bhs = 0u;
-    const uint32_t miss0 = int(threadIdx.x) < n_tab ? uint32_t(flags[kMissFlag + int(threadIdx.x)]) : 0u;
-    const int eb = native ? 0 : flags[0];
+    const int eb = flags[0];
     stats_fold<1024>(stats_a, n_a, alo, ahs);
     stats_fold<1024>(stats_b, n_b, blo, bhs);
     alo = wave_min(alo);
@@ -1410,8 +1332,6 @@ __global__ __launch_bounds__(1024) void path_flags_kernel(const uint32_t *__rest
     blo = wave_min(blo);
     bhs = wave_max(bhs);
     const int wave = int(threadIdx.x) >> 6;
-    const bool add = __builtin_amdgcn_ballot_w64((miss0 & kMissAdd) != 0u) == 0u;  // n_tab <= 16: the first wave's
-    const bool exact = __builtin_amdgcn_ballot_w64((miss0 & kMissExact) != 0u) == 0u;
     if ((threadIdx.x & 63) == 0) {
         red[wave][0] = alo;
         red[wave][1] = ahs;
@@ -1428,11 +1348,8 @@ __global__ __launch_bounds__(1024) void path_flags_kernel(const uint32_t *__rest
             b_lo = min(b_lo, red[w][2]);
             b_hs = max(b_hs, red[w][3]);
         }
-        // the native multiply's matrix cores need the exact product's window
-        const int kind = native ? kMmaExact : (add ? kMmaAdd : (exact ? kMmaExact : 0));
         int path, rounded;
-        decide_paths(eb, kind, false, a_lo, a_hs, b_lo, b_hs, true, narrow, path, rounded);
-        if (native) path = path == 2 + kMmaExact ? 3 : 0;
+        decide_paths(eb, 0, false, a_lo, a_hs, b_lo, b_hs, true, narrow, path, rounded);
         flags[1] = path;
         flags[2] = rounded;
     }
@@ -1445,14 +1362,14 @@ __global__ __launch_bounds__(1024) void path_flags_kernel(const uint32_t *__rest
 // the decode_a_body layouts) and the second operand's (decode_rows_body).  The jobs write
 // disjoint parts of the workspace.  The decode jobs' exponent statistics, which decide the table
 // kernel's path, are reduced by that kernel's own workgroups in a small call (tab_paths: nothing
-// runs between the two launches), else by path_flags_kernel or prep_rows_wide_kernel.
+// runs between the two launches), else by own_kernel or path_flags_kernel.
 struct PrepJobs {
     int n_tab, n_flag, n_a, n_b;  // workgroups of each job
     int wide;                     // the table job is a wide table's low-bits pass
     TablePrep t;
     ZeroTapFlags z;
     DecFmt fa, fb;
-    uint32_t *stats_a, *stats_b;  // decode statistics, or null (native multiply)
+    uint32_t *stats_a, *stats_b;  // decode statistics, or null (nothing is decided from them)
     DecRows b;
 };
 
@@ -1596,9 +1513,12 @@ inline DecFmt fmt_second(const Mode &md, const Plan &p, int m_bits)
 inline uint32_t *stats_a(char *ws, const Plan &p) { return reinterpret_cast<uint32_t *>(ws + p.off_stats); }
 inline uint32_t *stats_b(char *ws, const Plan &p) { return reinterpret_cast<uint32_t *>(ws + p.off_stats) + kStatSlots; }
 
+// Operands cast to fewer exponent bits than FP32's (no bf16 path; products scaled before the add).
+inline int narrow_of(const Mode &md) { return !md.native && md.e_bits < 8 ? 1 : 0; }
+
 // The jobs of a call of `macs` products, without the decodes' geometry: the table job (none for the native
-// multiply; M <= 7 writes the rows itself, a wide table's low-bits pass is followed by
-// prep_rows_wide_kernel), the statistics and the operand formats.
+// multiply; M <= 7 writes the rows itself, a wide table's low-bits pass is followed by own_kernel),
+// the statistics and the operand formats.
 PrepJobs prep_jobs(const Mode &md, const uint32_t *lut, int mb, char *ws, const Plan &p, double macs)
 {
     PrepJobs j{};
@@ -1617,7 +1537,7 @@ PrepJobs prep_jobs(const Mode &md, const uint32_t *lut, int mb, char *ws, const 
     j.t.hl_rows = reinterpret_cast<uint32_t *>(ws + p.off_hl_rows);
     if (p.rl == 7) {
         j.n_tab = table_jobs(mb);
-        j.t.kinds = small_call(macs, p.rl) ? 0 : 1;  // kTabApproxSelf has no body for them
+        j.t.kinds = small_call(macs, p.rl) || narrow_of(md) ? 0 : 1;  // no body for their kinds
     } else {
         j.wide = 1;
         j.t.part = reinterpret_cast<uint32_t *>(ws + p.off_wpart);
@@ -1635,29 +1555,19 @@ inline int tab_variant(const Mode &md, const Plan &p, double macs)
     return small_call(macs, p.rl) ? kTabApproxSelf : kTabApprox;
 }
 
-// Launches the pre-pass (first-operand decode a, lds its dynamic LDS bytes), then what the table
-// kernel variant `var` still needs: for a wide table the second table launch (which also writes
-// the path flags), for kTabApprox on rows of 128 entries the path flags.
+// Launches the pre-pass (first-operand decode a, lds its dynamic LDS bytes).
 template <class A>
-int run_prepass(const PrepJobs &j, const A &a, size_t lds, int var, int narrow, hipStream_t st)
+int run_prepass(const PrepJobs &j, const A &a, size_t lds, hipStream_t st)
 {
     const int blocks = j.n_tab + j.n_flag + j.n_a + j.n_b;
     hipLaunchKernelGGL((prepass_kernel<A>), dim3(unsigned(blocks)), dim3(256), lds, st, j, a);
-    if (j.wide) {
-        const int tiles = (1 << (j.t.m - 6)) * (1 << (j.t.m - 6));
-        hipLaunchKernelGGL(prep_rows_wide_kernel, dim3(std::min(tiles, 2048)), dim3(256), 0, st, j.t.lut, j.t.m,
-                           j.t.part, j.n_tab, j.stats_a, j.n_a, j.stats_b, j.n_b, narrow, j.t.rows, j.t.flags);
-    } else if (var != kTabApproxSelf && j.stats_a != nullptr) {
-        hipLaunchKernelGGL(path_flags_kernel, dim3(1), dim3(1024), 0, st, j.stats_a, j.n_a, j.stats_b, j.n_b, narrow,
-                           var == kTabNative ? 1 : 0, j.n_tab, j.t.flags);
-    }
     return launch_status();
 }
 
-// The path flags the split reduction reads: only the variant that reads them has written them.
-const int *reduce_flags(const PrepJobs &j, int var)
+// The path flags the split reduction reads: null where no body with splits of its own can have run.
+const int *reduce_flags(const PrepJobs &j, int var, const TabArgs &a)
 {
-    return var != kTabApproxSelf && j.stats_a != nullptr ? j.t.flags : nullptr;
+    return var != kTabApproxSelf && j.stats_a != nullptr && a.own_c != 0 ? j.t.flags : nullptr;
 }
 
 // The pointers of a launch's arguments (the rest is the plan's geometry, g).
@@ -1675,9 +1585,6 @@ TabArgs tab_args(TabArgs g, const Plan &p, int mb, char *ws, const uint32_t *A, 
     return a;
 }
 
-// Operands cast to fewer exponent bits than FP32's (no bf16 path; products scaled before the add).
-inline int narrow_of(const Mode &md) { return !md.native && md.e_bits < 8 ? 1 : 0; }
-
 // The table kernel's view of the decode statistics (kTabApproxSelf decides its path from them).
 void set_stats(TabArgs &a, const PrepJobs &j, const Mode &md)
 {
@@ -1686,7 +1593,8 @@ void set_stats(TabArgs &a, const PrepJobs &j, const Mode &md)
     a.n_a = j.n_a;
     a.n_b = j.n_b;
     a.narrow = narrow_of(md);
-    if (j.stats_a == nullptr) a.eb = nullptr;  // a small call with the native multiply: no flags
+    if (a.narrow && !j.wide) a.own_c = 0;  // no body for them on rows of 128 entries
+    if (j.stats_a == nullptr) a.eb = nullptr;  // a native multiply that decides nothing: no flags
 }
 
 // Products of a convolution pass (the same for the three passes).
@@ -1750,6 +1658,30 @@ class TimedLaunch {
     hipStream_t st_;
     long slot_ = -1;
 };
+
+// The launches between the pre-pass and the split reduction: for all but the calls that decide their path
+// in the table kernel (small_call) and the native multiply's that decide none, own_kernel, or
+// path_flags_kernel where it would only decide the path; then the table kernel.  own_kernel and the
+// table kernel are timed together.
+template <int OP>
+int run_table(const Plan &p, const PrepJobs &j, int var, const TabArgs &a, dim3 grid, int timer_kind, hipStream_t st)
+{
+    const bool decides = var != kTabApproxSelf && j.stats_a != nullptr, own = decides && (j.wide || a.own_c != 0);
+    if (decides && !own) {
+        hipLaunchKernelGGL(path_flags_kernel, dim3(1), dim3(1024), 0, st, j.stats_a, j.n_a, j.stats_b, j.n_b, a.narrow,
+                           j.t.flags);
+        if (launch_status() != AMSIM_OK) return AMSIM_ERR_HIP;
+    }
+    TimedLaunch tl(timer_kind, st);
+    if (own) {
+        const int cls = j.wide ? kOwnWide : (var == kTabNative ? kOwnNative : kOwnTab), nw = p.tile.nw;
+        const int64_t blocks = own_grid(a, nw, cls);
+        if (!own_grid_fits(blocks, nw)) return AMSIM_ERR_HIP;
+        const OwnPrep op{j.t.lut, j.t.part, j.wide ? j.n_tab : 0, j.wide ? 0 : j.n_tab, j.t.rows, j.t.flags};
+        if (own_launch<OP>(nw, cls, unsigned(blocks), a, op, st) != hipSuccess) return AMSIM_ERR_HIP;
+    }
+    return tab_launch<OP>(p.tile, p.rl, var, a, grid, st) == hipSuccess ? AMSIM_OK : AMSIM_ERR_HIP;
+}
 
 void destroy_events(KernelTimer &t)
 {
@@ -1928,22 +1860,14 @@ int gemm_run(const Mode &md, int trans_a, int trans_b, int64_t m, int64_t n, int
     j.b = DecRows{B, 0, b_sr, b_sc, 1, int(k), int(k), int(n), Bd, int(p.b_ld), decode_vec(B, 0, b_sr, b_sc)};
     j.n_b = decode_grid(k * p.b_ld);
     const int var = tab_variant(md, p, double(m) * double(n) * double(k));
-    if (run_prepass(j, da, 0, var, narrow_of(md), st) != AMSIM_OK) return AMSIM_ERR_HIP;
-    int rc;
-    {
-        TabArgs a = tab_args(gemm_geom(p, m, n, k, ldc), p, mb, ws, Ad, Bd, out);
-        set_stats(a, j, md);
-        set_format_scales(a, md);
-        const dim3 grid = dim3_of(gemm_grid(p));
-        TimedLaunch tl(timer_kind, st);
-        rc = tab_launch<OP_GEMM>(p.tile, p.rl, var, a, grid, st) == hipSuccess
-                 ? AMSIM_OK
-                 : AMSIM_ERR_HIP;
-    }
-    if (rc != AMSIM_OK) return AMSIM_ERR_HIP;
+    if (run_prepass(j, da, 0, st) != AMSIM_OK) return AMSIM_ERR_HIP;
+    TabArgs a = tab_args(gemm_geom(p, m, n, k, ldc), p, mb, ws, Ad, Bd, out);
+    set_stats(a, j, md);
+    set_format_scales(a, md);
+    if (run_table<OP_GEMM>(p, j, var, a, dim3_of(gemm_grid(p)), timer_kind, st) != AMSIM_OK) return AMSIM_ERR_HIP;
     if (p.splits > 1) {
         launch_reduce(reinterpret_cast<const float *>(ws + p.off_part), p.splits, int(m), int(n), C, ldc, st,
-                      reduce_flags(j, var), p.own_splits);
+                      reduce_flags(j, var, a), p.own_splits);
         if (launch_status() != AMSIM_OK) return AMSIM_ERR_HIP;
     }
     return AMSIM_OK;
@@ -2039,26 +1963,20 @@ int fwd_core(const Mode &md, const amsim_conv2d *desc, const float *x, const flo
     if (p.unfold_w) {
         j.n_a = int(std::min<int64_t>(int64_t(s.n) * p.Hp, kStatSlots));  // one padded image row at a time
         const DecUnfold da{x, s.n, s.h, s.w, s.ci, s.pt, s.pl, p.Hp, s.kw, s.sw, s.ow, Xd};
-        rc = run_prepass(j, da, size_t(s.w) * s.ci * 4, var, narrow_of(md), st);
+        rc = run_prepass(j, da, size_t(s.w) * s.ci * 4, st);
     } else {
         size_t lds;
         const DecNhcw da = nhcw_job(x, s.n, s.h, s.w, s.ci, s.pt, s.pl, p.Hp, p.Wp, Xd, p.rec_c, &j.n_a, &lds);
-        rc = run_prepass(j, da, lds, var, narrow_of(md), st);
+        rc = run_prepass(j, da, lds, st);
     }
     if (rc != AMSIM_OK) return AMSIM_ERR_HIP;
     TabArgs a = tab_args(fwd_geom(p, s), p, mb, ws, Xd, Wd, out);
     set_stats(a, j, md);
     set_format_scales(a, md);
-    const dim3 grid = dim3_of(fwd_grid(p, s));
-    {
-        TimedLaunch tl(timer_kind, st);
-        rc = tab_launch<OP_FWD>(p.tile, p.rl, var, a, grid, st) == hipSuccess
-                 ? AMSIM_OK
-                 : AMSIM_ERR_HIP;
-    }
+    rc = run_table<OP_FWD>(p, j, var, a, dim3_of(fwd_grid(p, s)), timer_kind, st);
     if (rc != AMSIM_OK || p.splits == 1) return rc;
     launch_reduce(reinterpret_cast<const float *>(ws + p.off_part), p.splits, int(rows), s.co, y, int64_t(s.co), st,
-                  reduce_flags(j, var), p.own_splits);
+                  reduce_flags(j, var, a), p.own_splits);
     return launch_status();
 }
 
@@ -2094,21 +2012,16 @@ int bwd_data_run(const Mode &md, const amsim_conv2d *desc, const Plan &p, const 
     j.b = DecRows{w, int64_t(s.ci) * s.co, 1, int64_t(s.co), s.kh * s.kw, s.co, s.co, s.ci, Wtd, int(p.b_ld), 0};
     j.n_b = decode_grid(int64_t(s.kh) * s.kw * s.co * p.b_ld);
     const int var = tab_variant(md, p, conv_macs(s));
-    if (run_prepass(j, da, lds, var, narrow_of(md), st) != AMSIM_OK) return AMSIM_ERR_HIP;
+    if (run_prepass(j, da, lds, st) != AMSIM_OK) return AMSIM_ERR_HIP;
     TabArgs a = tab_args(bwd_data_geom(p, s), p, mb, ws, Dyd, Wtd, out);
     set_stats(a, j, md);
     set_format_scales(a, md);
-    const dim3 grid = dim3_of(bwd_data_grid(p, s));
-    {
-        TimedLaunch tl(md.native ? AMSIM_KERNEL_CONV_BWD_DATA_NATIVE : AMSIM_KERNEL_CONV_BWD_DATA, st);
-        rc = tab_launch<OP_BWD_DATA>(p.tile, p.rl, var, a, grid, st) == hipSuccess
-                 ? AMSIM_OK
-                 : AMSIM_ERR_HIP;
-    }
+    rc = run_table<OP_BWD_DATA>(p, j, var, a, dim3_of(bwd_data_grid(p, s)),
+                                md.native ? AMSIM_KERNEL_CONV_BWD_DATA_NATIVE : AMSIM_KERNEL_CONV_BWD_DATA, st);
     if (rc != AMSIM_OK) return rc;
     if (p.splits > 1) {
         launch_reduce(reinterpret_cast<const float *>(ws + p.off_part), p.splits, s.n * s.h * s.w, s.ci, dx,
-                      int64_t(s.ci), st, reduce_flags(j, var), p.own_splits);
+                      int64_t(s.ci), st, reduce_flags(j, var, a), p.own_splits);
         if (launch_status() != AMSIM_OK) return AMSIM_ERR_HIP;
     }
     if (fixup && s.sh * s.sw > 1) {  // the taps outside each output's stride phase (dilation zeros)
@@ -2183,23 +2096,18 @@ int conv_bwd_weight_run(const Mode &md, const amsim_conv2d *desc, const float *x
     j.b = DecRows{dy, 0, int64_t(s.co), 1, 1, int(npo), int(npo), s.co, Dyd, int(p.b_ld), decode_vec(dy, 0, s.co, 1)};
     j.n_b = decode_grid(npo * p.b_ld);
     const int var = tab_variant(md, p, conv_macs(s));
-    if (run_prepass(j, da, row_lds ? size_t(wc) * 4 : 0, var, narrow_of(md), st) != AMSIM_OK) return AMSIM_ERR_HIP;
+    if (run_prepass(j, da, row_lds ? size_t(wc) * 4 : 0, st) != AMSIM_OK) return AMSIM_ERR_HIP;
     const int R = s.kh * s.kw * s.ci;
     float *out = p.splits > 1 ? reinterpret_cast<float *>(ws + p.off_part) : dw;
-    {
-        TimedLaunch tl(md.native ? AMSIM_KERNEL_CONV_BWD_WEIGHT_NATIVE : AMSIM_KERNEL_CONV_BWD_WEIGHT, st);
-        TabArgs a = tab_args(bwd_weight_geom(p, s), p, mb, ws, Xd, Dyd, out);
-        set_stats(a, j, md);
-        set_format_scales(a, md);
-        const dim3 grid = dim3_of(bwd_weight_grid(p, s));
-        rc = tab_launch<OP_BWD_WEIGHT>(p.tile, p.rl, var, a, grid, st) == hipSuccess
-                 ? AMSIM_OK
-                 : AMSIM_ERR_HIP;
-    }
+    TabArgs a = tab_args(bwd_weight_geom(p, s), p, mb, ws, Xd, Dyd, out);
+    set_stats(a, j, md);
+    set_format_scales(a, md);
+    rc = run_table<OP_BWD_WEIGHT>(p, j, var, a, dim3_of(bwd_weight_grid(p, s)),
+                                  md.native ? AMSIM_KERNEL_CONV_BWD_WEIGHT_NATIVE : AMSIM_KERNEL_CONV_BWD_WEIGHT, st);
     if (rc != AMSIM_OK) return AMSIM_ERR_HIP;
     if (p.splits > 1) {
         launch_reduce(reinterpret_cast<const float *>(ws + p.off_part), p.splits, R, s.co, dw, int64_t(s.co), st,
-                      reduce_flags(j, var), p.own_splits);
+                      reduce_flags(j, var, a), p.own_splits);
         return launch_status();
     }
     return AMSIM_OK;

@@ -160,7 +160,7 @@ struct Plan {
     int splits;           // reduction splits
     int chunks_per_split;   // 8-step reduction chunks per split
     int64_t own_rows, own_n, own_phases, own_q;  // bodies with tiles of their own: the result and its chunks,
-    int own_c, own_splits, own_cps;  // tile width code (own_cols) and the same for the bodies with tiles of their own (plan_own_tiles)
+    int own_c, own_splits, own_cps;  // tile width code (own_cols), splits and chunks per split of those bodies (plan_own_tiles)
     int64_t out_elems;      // elements of the result (partial sums hold splits of them)
     int Hp, Wp, OHp, OWp, pad_oh, pad_ow;
     bool unfold_w;          // forward / backward-data pass over x unfolded along w
@@ -240,7 +240,6 @@ inline bool valid_m(int m_bits) { return m_bits >= 1 && m_bits <= 11; }
 constexpr size_t kDotRowsBytes = size_t(kZeroRow + 1) * kTabRowEntries;
 constexpr size_t kHlRowsBytes = size_t(kZeroRow + 1) * kHlRowBytes;  // 2-byte tables, hi/lo path
 constexpr size_t kStatsBytes = size_t(2) * kStatSlots * 4;
-constexpr int kWidePartWords = 1024;
 
 inline size_t rows_bytes(int rl) { return (size_t(1) << rl) * ((size_t(1) << rl) + (rl == 7 ? 1 : 0)) * 4; }
 
@@ -438,7 +437,7 @@ inline void plan_native_tiles(Plan &p)
     plan_own_tiles(p, p.own_rows, p.own_n, p.own_phases, p.own_q, true, most);
 }
 
-// Room for partial sums of the own-tile bodies: up to 64 MiB, or what the gathers' splits take.
+// Room for partial sums of the bodies with tiles of their own: up to 64 MiB, or what the gathers' splits take.
 inline int64_t own_most(const Plan &p)
 {
     return std::max<int64_t>(p.splits, (int64_t(64) << 20) / (p.out_elems * 4));
@@ -695,6 +694,7 @@ inline TabArgs tab_geom(const Plan &p, int64_t a_elems, int R, int N)
     a.splits = p.splits;
     a.chunk = p.chunk;
     a.chunks_per_split = p.chunks_per_split;
+    a.phases = int(p.own_phases);
     a.own_c = p.own_c;
     a.own_splits = p.own_splits;
     a.own_cps = p.own_cps;
@@ -706,6 +706,19 @@ inline TabArgs tab_geom(const Plan &p, int64_t a_elems, int R, int N)
     a.sd = 1.0f;
     return a;
 }
+
+// Workgroups of own_kernel for a call's arguments: one per tile, rounded up to keep the XCD order
+// (own_tile_id), and for wide tables at least one per 64 x 64 block of the table, up to what the CUs' LDS
+// holds, to transpose it (16 blocks at M = 8: more than the one workgroup that only decides).
+inline int64_t own_grid(const TabArgs &a, int nw, int cls)
+{
+    int64_t blocks = std::max<int64_t>(1, own_tiles(a, nw));
+    if (blocks > 8) blocks = round_up(blocks, 8);
+    if (cls == kOwnWide) blocks = std::max(blocks, std::min<int64_t>(int64_t(1) << (2 * (a.m - 6)), nw == 8 ? 512 : 768));
+    return blocks;
+}
+// HIP's limit on a launch's threads.
+inline bool own_grid_fits(int64_t blocks, int nw) { return blocks * 64 * nw < int64_t(1) << 32; }
 
 // GEMM: m x n result with leading dimension ldc, reduction k.
 inline TabArgs gemm_geom(const Plan &p, int64_t m, int64_t n, int64_t k, int64_t ldc)

@@ -61,10 +61,11 @@ struct TabArgs {
     const unsigned char *rows;      // transposed table rows (exact path)
     const unsigned char *dot_rows;  // the same 1-byte rows in bf16-path staging order
     const unsigned char *hl_rows;   // 2-byte tables: entries split into bf16 halves (hi/lo path)
-    const int *eb;                  // [0] entry width, [1] 1 (2) when the bf16 (hi/lo) path may run, 3 or 4
-                                    // for the matrix-core bodies, [2] 1 when the exact path rounds each
-                                    // product before adding it, [3] (rows of 256 entries or more) 1 when
-                                    // the table is sum-indexed
+    const int *eb;                  // flags: [0] entry width, [1] the call's path (decide_paths): 3 or more
+                                    // for a body with tiles of its own, 1 (2) for the bf16 (hi/lo) path,
+                                    // [2] 1 when the exact path rounds each product before adding it,
+                                    // [3] (rows of 256 entries or more) 1 when the table is sum-indexed.
+                                    // Null: a native multiply without a body with tiles of its own
     const uint32_t *stats_a, *stats_b;  // kTabApproxSelf: the decode passes' exponent statistics
     int n_a, n_b;                       // (null: none), words of each operand, and whether the
     int narrow;                         // operands are cast to fewer exponent bits than FP32's
@@ -75,7 +76,8 @@ struct TabArgs {
     int m;               // mantissa bits of the table index
     int chunk;           // steps per reduction chunk (8)
     int chunks_per_split;  // reduction chunks per split
-    int own_c;             // bodies with tiles of their own: tile width (own_cols),
+    int phases;            // stride phases (backward data; else 1)
+    int own_c;             // bodies with tiles of their own: tile width (own_cols; 0: the call has none),
     int own_splits, own_cps;  // splits and chunks per split
     int64_t out_elems;   // elements of one split's partial result (splits > 1)
     int Mp, K;           // GEMM
@@ -86,7 +88,6 @@ struct TabArgs {
     int csplit;          // FWD / BWD_DATA: channel chunks; taps run chunk-major (csplit divides s.ci / s.co
                          // into multiples of 8)
     int OHp, OWp, pad_oh, pad_ow;  // zero-padded dy (BWD_DATA)
-    int gx, gy, gz;      // the launch's tiles: row blocks, column blocks, phases x splits
     int tx, ty, tz;      // this workgroup's tile (row block, column block, phase/split); set on entry
 };
 
@@ -95,46 +96,58 @@ struct TabArgs {
 // (phases differ in work, so each XCD gets all of them), then column blocks, row blocks, splits --
 // so that the workgroups an XCD runs together share first-operand rows and second-operand cache
 // lines in its L2.  Grids whose size is not a multiple of 8 keep the hardware order.
-__device__ __forceinline__ bool tab_tile_id(TabArgs &a)
+__device__ __forceinline__ void tab_tile_id(int splits, int &tx, int &ty, int &tz)
 {
-    const uint32_t gx = uint32_t(a.gx), gy = uint32_t(a.gy), gz = uint32_t(a.gz), n = gx * gy * gz;
-    const uint32_t id = blockIdx.x;
-    if (id >= n) return false;
+    const uint32_t gx = gridDim.x, gy = gridDim.y, gz = gridDim.z, n = gx * gy * gz;
+    const uint32_t id = blockIdx.x + gx * (blockIdx.y + gy * blockIdx.z);
     if (n % 8u != 0u) {
-        a.tx = int(id % gx);
-        a.ty = int((id / gx) % gy);
-        a.tz = int(id / (gx * gy));
-        return true;
+        tx = int(blockIdx.x);
+        ty = int(blockIdx.y);
+        tz = int(blockIdx.z);
+        return;
     }
     const uint32_t lid = (id % 8u) * (n / 8u) + id / 8u;
-    const uint32_t phases = gz / uint32_t(a.splits);
+    const uint32_t phases = gz / uint32_t(splits);
     const uint32_t ph = lid % phases, rest = lid / phases;
-    a.ty = int(rest % gy);
-    a.tx = int((rest / gy) % gx);
-    a.tz = int(ph * uint32_t(a.splits) + rest / (gx * gy));
-    return true;
+    ty = int(rest % gy);
+    tx = int((rest / gy) % gx);
+    tz = int(ph * uint32_t(splits) + rest / (gx * gy));
 }
 
-// Columns of such a body's tiles, of width code c: the matrix-core bodies' WC (4 or 2) or the arithmetic
-// bodies' TN (8 or 4).
+// Columns of the tiles of a body with tiles of its own (own_kernel), of width code c: the matrix-core
+// bodies' WC (4 or 2), the arithmetic and native bodies' TN (8 or 4).
 __host__ __device__ constexpr int own_cols(int c) { return 16 * c; }
 
-// The workgroup's tile (tx, ty) of a body that tiles and splits the result its own way, nrow x ncol
-// tiles per phase and split, a.tz and the body's splits in a: contiguous ranges of tiles per XCD, in tab_tile_id's order.  False for a
-// workgroup past the last tile.
-__device__ __forceinline__ bool own_tile(TabArgs &a, int nrow, int ncol, int &tx, int &ty)
+// Workgroup id of `grid` -> tile lid of `tiles`: contiguous ranges of tiles per XCD where the grid is a
+// multiple of 8 (own_grid).  False for a workgroup past the last tile.
+__host__ __device__ __forceinline__ bool own_tile_id(uint32_t id, uint32_t grid, uint32_t tiles, uint32_t &lid)
 {
-    const uint32_t phases = uint32_t(a.gz) / uint32_t(a.splits);
-    a.splits = a.own_splits;
-    a.chunks_per_split = a.own_cps;
-    const uint32_t tiles = uint32_t(nrow) * uint32_t(ncol) * phases * uint32_t(a.splits);
-    uint32_t id = blockIdx.x;
-    if (gridDim.x % 8u == 0u) {
+    lid = id;
+    if (grid % 8u == 0u) {
         const uint32_t per = (tiles + 7u) / 8u;
         if (id / 8u >= per) return false;
-        id = (id % 8u) * per + id / 8u;
+        lid = (id % 8u) * per + id / 8u;
     }
-    if (id >= tiles) return false;
+    return lid < tiles;
+}
+
+// Tiles of such a body for a call's arguments, in workgroups of nw waves (32 nw rows).
+__host__ __device__ __forceinline__ uint32_t own_tiles(const TabArgs &a, int nw)
+{
+    if (a.own_c == 0) return 0u;
+    return uint32_t((a.R + 32 * nw - 1) / (32 * nw)) * uint32_t((a.N + own_cols(a.own_c) - 1) / own_cols(a.own_c)) *
+           uint32_t(a.phases) * uint32_t(a.own_splits);
+}
+
+// The workgroup's tile (tx, ty) of such a body, nrow x ncol tiles per phase and split, a.tz and the
+// body's splits in a, in tab_tile_id's order.
+__device__ __forceinline__ bool own_tile(TabArgs &a, int nrow, int ncol, int &tx, int &ty)
+{
+    const uint32_t phases = uint32_t(a.phases);
+    a.splits = a.own_splits;
+    a.chunks_per_split = a.own_cps;
+    uint32_t id;
+    if (!own_tile_id(blockIdx.x, gridDim.x, uint32_t(nrow) * uint32_t(ncol) * phases * uint32_t(a.splits), id)) return false;
     const uint32_t ph = id % phases, rest = id / phases;
     ty = int(rest % uint32_t(ncol));
     const int rest2 = int(rest / uint32_t(ncol));
@@ -1089,7 +1102,8 @@ __device__ __forceinline__ void tab_body_native_mma(const TabArgs &a0)
         const bool colok = col < a.N;
 #pragma unroll
         for (int r = 0; r < RB; ++r) {
-            const int row0 = roww + wr0 + r * 32 + 4 * hk;
+            int row0 = roww + wr0 + r * 32 + 4 * hk;
+            asm volatile("" : "+v"(row0));  // the rows' offsets anew for each column block: kept, they spill
             uint32_t pending = 0u;
 #pragma unroll
             for (int i = 0; i < 16; ++i)
@@ -2294,6 +2308,28 @@ __device__ __forceinline__ void stats_fold(const uint32_t *__restrict__ stats, i
     }
 }
 
+// The same over all kStatSlots words of an operand's statistics in 16-byte loads, those of a whole
+// operand in flight at once (NT >= 256 threads): the words past n hold anything and are not used.
+template <int NT>
+__device__ __forceinline__ void stats_fold_wide(const uint32_t *__restrict__ stats, int n, uint32_t &lo, uint32_t &hs)
+{
+    constexpr int U = kStatSlots / (4 * NT);
+    u32x4 v[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const int i = (int(threadIdx.x) + u * NT) * 4;
+        v[u] = i < n ? *reinterpret_cast<const u32x4 *>(stats + i) : u32x4{0xFFu, 0xFFu, 0xFFu, 0xFFu};
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const uint32_t w = (int(threadIdx.x) + u * NT) * 4 + e < n ? v[u][e] : 0xFFu;
+            lo = min(lo, w & 0xFFu);
+            hs = max(hs, (w >> 8) & 0x1FFu);
+        }
+}
+
 // The path decided by every workgroup of a kTabApproxSelf kernel at its start, from the decode
 // statistics (a.n_a + a.n_b words) -- so that no launch sits between the pre-pass and the table
 // kernel.  NW: waves of the workgroup; red: 4 NW + 2 words of LDS, free until the body's first
@@ -2338,19 +2374,25 @@ __device__ __forceinline__ void tab_paths(const TabArgs &a, int eb, uint32_t *re
     __syncthreads();  // the body's first LDS stores may overwrite red
 }
 
+// Whether own_kernel computed the call (flags): read through a pointer of its own, so that the path read
+// again further on leaves the bodies compiled as without this test.
+__device__ __forceinline__ bool own_ran(const int *flags)
+{
+    auto f = (const __attribute__((address_space(1))) int *)flags;
+    asm volatile("" : "+s"(f));
+    return __builtin_amdgcn_readfirstlane(f[1]) >= 3;
+}
+
 template <int OP, int TM, int TN, int WR, int NW, int RL, int VAR>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(4, 4))) void tab_kernel(TabArgs args)
 {
+    if constexpr (VAR == kTabApprox)
+        if (own_ran(args.eb)) return;
     TabArgs a = args;
+    tab_tile_id(a.splits, a.tx, a.ty, a.tz);
     if constexpr (VAR == kTabNative) {
-        if (a.eb != nullptr && __builtin_amdgcn_readfirstlane(a.eb[1]) == 3) {  // a large call
-            if (a.own_c == 8)
-                tab_body_native_mma<OP, NW, 8>(a);
-            else
-                tab_body_native_mma<OP, NW, 4>(a);
-            return;
-        }
-        if (tab_tile_id(a)) tab_body_native<OP, TM, TN, WR, NW>(a);
+        if (a.eb != nullptr && own_ran(a.eb)) return;
+        tab_body_native<OP, TM, TN, WR, NW>(a);
         return;
     }
     const int eb = __builtin_amdgcn_readfirstlane(a.eb[0]);
@@ -2359,32 +2401,8 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(4, 4)))
         extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
         tab_paths<NW>(a, eb, reinterpret_cast<uint32_t *>(smem), self_path, self_rounded);
     }
-    const int path = VAR == kTabApproxSelf ? self_path : __builtin_amdgcn_readfirstlane(a.eb[1]);
-    if constexpr (RL == 7 && VAR == kTabApprox) {
-        if (path == 2 + kMmaAdd) {
-            tab_mma<OP, NW, kMmaAdd>(a);
-            return;
-        }
-        if (path == 2 + kMmaExact) {
-            tab_mma<OP, NW, kMmaExact>(a);
-            return;
-        }
-    }
-    if constexpr (RL >= 8) {
-        if (path >= 3) {
-            if (path == 3)
-                tab_arith<OP, NW, kMmaAdd, false>(a);
-            else if (path == 4)
-                tab_arith<OP, NW, kMmaExact, false>(a);
-            else if (path == 5)
-                tab_arith<OP, NW, kMmaAdd, true>(a);
-            else
-                tab_arith<OP, NW, kMmaExact, true>(a);
-            return;
-        }
-    }
-    if (!tab_tile_id(a)) return;
     if constexpr (RL == 7 && dot_cols_ok(TN) && WR == NW) {
+        const int path = VAR == kTabApproxSelf ? self_path : __builtin_amdgcn_readfirstlane(a.eb[1]);
         if (path == 1) {
             tab_body_dot<OP, TM, NW, TN>(a);
             return;
@@ -2434,8 +2452,7 @@ constexpr size_t tab_exact_lds_bytes(int tnw, int rl, int eb)
 
 constexpr size_t tab_native_lds_bytes(int tn, int wr, int nw)
 {
-    const size_t v = size_t(2) * kNativeSlabSteps * tn * (nw / wr) * 4, mma = size_t(2) * nat_buf_bytes(nw, 8);
-    return v > mma ? v : mma;
+    return size_t(2) * kNativeSlabSteps * tn * (nw / wr) * 4;
 }
 
 constexpr size_t tab_lds_bytes(int tn, int wr, int nw, int rl)
@@ -2446,13 +2463,202 @@ constexpr size_t tab_lds_bytes(int tn, int wr, int nw, int rl)
     b = tab_exact_lds_bytes(tnw, rl, 4) > b ? tab_exact_lds_bytes(tnw, rl, 4) : b;
     const size_t dot = (rl == 7 && dot_cols_ok(tn) && wr == nw) ? size_t(2) * dot_slab_steps(nw) * kDotStepBytes : 0;
     const size_t hl = (rl == 7 && tn == 8 && (nw == 8 || nw == 4) && wr == nw) ? size_t(2) * nw * kHlStepBytes : 0;
-    const size_t arith = rl >= 8 ? arith_lds_bytes(nw) : 0;
-    const size_t sum0 = rl >= 8 ? tab_sum_lds_bytes(tnw, rl) : 0, sum = sum0 > arith ? sum0 : arith;
+    const size_t sum = rl >= 8 ? tab_sum_lds_bytes(tnw, rl) : 0;
     b = b > dot ? b : dot;
     b = b > sum ? b : sum;
-    const size_t mma = rl == 7 ? mma_lds_bytes(nw) : 0;
-    b = b > mma ? b : mma;
     return b > hl ? b : hl;
+}
+
+// ------------------------------------------------- the bodies with tiles of their own
+// own_kernel runs between the pre-pass and the table kernel: it decides the call's path, and computes
+// the call itself where one of the bodies with tiles of its own does; the table kernel of such a call
+// finds path 3 or more in the flags and returns at once (1.3 us on MI355X).  Apart from that kernel
+// because both lose in one: with these bodies inlined into it the table kernel had 124 to 128 VGPRs and
+// up to 300 spilled SGPRs for every tile (from 43 up without them), and general tables paid: the GEMM
+// 1024^3 with a 2-byte table at M = 7 133 -> 141 us, a 3x3 48 -> 32 channel backward-data pass at
+// M = 11 110 -> 140 us.  The launch takes the place of one that decided the path alone.
+//
+// CLS: kOwnTab (M <= 7), kOwnWide (M = 8..11) or kOwnNative.
+//   kOwnTab: the kinds of table that the pre-pass's n_tab table workgroups rule out are in
+//     flags[kMissFlag ...]; where both are, only workgroup 0 goes on, to decide between the gathers' paths.
+//   kOwnWide: the nparts words of lut_low_bits_body give the entry width and the kind.  A table of no
+//     kind is transposed by the other workgroups:
+//     row kb (2^m entries of eb bytes) holds entry (ka, kb) at byte ka * eb, through 64 x 64 LDS tiles
+//     (loads along kb, stores along ka).
+//   kOwnNative: the matrix cores' window.
+// Workgroup 0 writes flags[1], the path, and flags[2], the exact path's product form; kOwnWide also
+// flags[0], the entry width, and flags[3], whether the table is sum-indexed.
+enum { kOwnTab = 0, kOwnWide = 1, kOwnNative = 2 };
+// Kinds of table an entry rules out (table_misses), and that the table is sum-indexed.
+constexpr uint32_t kMissAdd = 0x80000000u, kMissExact = 0x40000000u, kMissSum = 0x20000000u;
+constexpr int kMissFlag = 16;  // of the flags' 64 words, one per table workgroup (table_jobs) from here
+
+struct OwnPrep {
+    const uint32_t *lut;
+    const uint32_t *part;  // kOwnWide: lut_low_bits_body's words
+    int nparts;
+    int n_tab;             // kOwnTab: table workgroups of the pre-pass
+    unsigned char *rows;   // kOwnWide: the transposed rows
+    int *flags;
+};
+
+constexpr int kRowTile = 64;  // entries along each side of kOwnWide's transposing tile
+constexpr size_t own_lds_bytes(int nw, int cls)
+{
+    const size_t rows = size_t(kRowTile) * (kRowTile + 1) * 4, arith = arith_lds_bytes(nw);
+    return cls == kOwnTab ? mma_lds_bytes(nw) : (cls == kOwnNative ? size_t(2) * nat_buf_bytes(nw, 8) : (arith > rows ? arith : rows));
+}
+
+template <int OP, int NW, int CLS>
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(4, 4))) void own_kernel(TabArgs a, OwnPrep p)
+{
+    constexpr int NT = 64 * NW;
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    uint32_t *red = reinterpret_cast<uint32_t *>(smem);  // 5 NW words, free until the body
+    const int lane = int(threadIdx.x) & 63, wave = wave_id();
+    const bool lead = blockIdx.x == 0;
+    uint32_t lb = 0u;  // the table's low bits and misses
+    int eb = 0;
+    if constexpr (CLS == kOwnTab) {
+        lb = lane < p.n_tab ? uint32_t(p.flags[kMissFlag + lane]) : 0u;  // n_tab <= 16
+        eb = p.flags[0];
+    } else if constexpr (CLS == kOwnWide) {
+#pragma unroll
+        for (int k = 0; k < kWidePartWords / NT; ++k) {
+            const int i = int(threadIdx.x) + k * NT;
+            if (i < p.nparts) lb |= p.part[i];
+        }
+    }
+    uint32_t alo = 255u, ahs = 0u, blo = 255u, bhs = 0u;
+    auto fold = [&]() __attribute__((always_inline)) {
+        stats_fold_wide<NT>(a.stats_a, a.n_a, alo, ahs);
+        stats_fold_wide<NT>(a.stats_b, a.n_b, blo, bhs);
+    };
+    const bool few = a.n_a + a.n_b <= 2048;  // 8 KiB: read along with the above, whatever the kind
+    if (few) fold();
+    if constexpr (CLS == kOwnTab) {
+        lb = (__builtin_amdgcn_ballot_w64((lb & kMissAdd) != 0u) != 0u ? kMissAdd : 0u) |
+             (__builtin_amdgcn_ballot_w64((lb & kMissExact) != 0u) != 0u ? kMissExact : 0u);
+        eb = __builtin_amdgcn_readfirstlane(eb);
+    } else if constexpr (CLS == kOwnWide) {
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) lb |= uint32_t(__shfl_xor(int(lb), o));
+        if (lane == 0) red[4 * NW + wave] = lb;
+        __syncthreads();
+#pragma unroll
+        for (int w = 0; w < NW; ++w) lb |= red[4 * NW + w];
+        lb = __builtin_amdgcn_readfirstlane(lb);
+        eb = (lb & 0xFFFFu) == 0u ? 1 : ((lb & 0xFFu) == 0u ? 2 : 4);
+    }
+    // the native multiply's matrix cores need the exact product's window
+    const int kind = a.own_c == 0 ? 0
+                     : CLS == kOwnNative ? kMmaExact
+                     : (lb & kMissAdd) == 0u ? kMmaAdd
+                     : (lb & kMissExact) == 0u ? kMmaExact : 0;
+    uint32_t id;
+    const bool tiled = own_tile_id(blockIdx.x, gridDim.x, own_tiles(a, NW), id);
+    int path = 0;
+    if (lead || (kind != 0 && tiled)) {  // uniform over the workgroup
+        if (!few) fold();
+        alo = wave_min(alo);
+        ahs = wave_max(ahs);
+        blo = wave_min(blo);
+        bhs = wave_max(bhs);
+        if (lane == 0) {
+            red[4 * wave + 0] = alo;
+            red[4 * wave + 1] = ahs;
+            red[4 * wave + 2] = blo;
+            red[4 * wave + 3] = bhs;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int w = 0; w < NW; ++w) {
+            alo = min(alo, red[4 * w + 0]);
+            ahs = max(ahs, red[4 * w + 1]);
+            blo = min(blo, red[4 * w + 2]);
+            bhs = max(bhs, red[4 * w + 3]);
+        }
+        int rounded;
+        decide_paths(eb, kind, CLS == kOwnWide, alo, ahs, blo, bhs, true, a.narrow, path, rounded);
+        if (CLS == kOwnNative) path = path == 2 + kMmaExact ? 3 : 0;
+        path = __builtin_amdgcn_readfirstlane(path);
+        if (lead && threadIdx.x == 0) {
+            p.flags[1] = path;
+            p.flags[2] = rounded;
+            if constexpr (CLS == kOwnWide) {
+                p.flags[0] = eb;
+                p.flags[3] = (lb & kMissSum) == 0u ? 1 : 0;
+            }
+        }
+        __syncthreads();  // red has been read: the body's first LDS stores may overwrite it
+    }
+    if (path >= 3) {
+        // vmcnt(0): every load of another part of this kernel has come in.  Without it the compiler waits
+        // for some of them in the bodies' loops, and so for the next slab's loads there (rounded exact
+        // products at M = 10: 120 -> 130 us)
+        __builtin_amdgcn_s_waitcnt(0x0F70);
+        if constexpr (CLS == kOwnTab) {
+            if (path == 2 + kMmaAdd)
+                tab_mma<OP, NW, kMmaAdd>(a);
+            else
+                tab_mma<OP, NW, kMmaExact>(a);
+        } else if constexpr (CLS == kOwnNative) {
+            if (a.own_c == 8)
+                tab_body_native_mma<OP, NW, 8>(a);
+            else
+                tab_body_native_mma<OP, NW, 4>(a);
+        } else {
+            if (path == 3)
+                tab_arith<OP, NW, kMmaAdd, false>(a);
+            else if (path == 4)
+                tab_arith<OP, NW, kMmaExact, false>(a);
+            else if (path == 5)
+                tab_arith<OP, NW, kMmaAdd, true>(a);
+            else
+                tab_arith<OP, NW, kMmaExact, true>(a);
+        }
+        return;
+    }
+    if constexpr (CLS == kOwnWide) {
+        if (kind != 0 || lead) return;  // no row is read; workgroup 0 has decided in the meantime
+        uint32_t(*tile)[kRowTile + 1] = reinterpret_cast<uint32_t(*)[kRowTile + 1]>(smem);
+        const int n = 1 << a.m, tiles_1d = n / kRowTile, tiles = tiles_1d * tiles_1d, step = int(gridDim.x) - 1;
+        // a sum-indexed table's entries are read at kb = 0 and at ka = 2^m - 1 only
+        const bool sum = (lb & kMissSum) == 0u;
+        auto skipped = [&](int t) { return sum && t % tiles_1d != 0 && t / tiles_1d != tiles_1d - 1; };
+        uint32_t in[kRowTile / NW];  // a block [ka][kb], its loads in flight while the one before it is written
+        auto load = [&](int t) __attribute__((always_inline)) {
+            if (t >= tiles || skipped(t)) return;
+            const uint32_t *src = p.lut + size_t(t / tiles_1d * kRowTile + wave) * n + t % tiles_1d * kRowTile + lane;
+#pragma unroll
+            for (int k = 0; k < kRowTile / NW; ++k) in[k] = src[size_t(k) * NW * n];
+        };
+        load(int(blockIdx.x) - 1);
+        for (int t = int(blockIdx.x) - 1; t < tiles; t += step) {
+            const bool skip = skipped(t);  // uniform
+            if (!skip) {
+#pragma unroll
+                for (int k = 0; k < kRowTile / NW; ++k) tile[wave + k * NW][lane] = in[k];
+            }
+            load(t + step);
+            if (skip) continue;
+            __syncthreads();
+            const int ka0 = t / tiles_1d * kRowTile, kb0 = t % tiles_1d * kRowTile;
+#pragma unroll
+            for (int k = 0; k < kRowTile / NW; ++k) {
+                const int i = wave + k * NW;
+                const uint32_t e = tile[lane][i] & 0x00FFFFFFu;  // entry (ka0 + lane, kb0 + i)
+                unsigned char *row = p.rows + size_t(kb0 + i) * n * eb;
+                if (eb == 1)
+                    row[ka0 + lane] = static_cast<unsigned char>(e >> 16);
+                else if (eb == 2)
+                    reinterpret_cast<uint16_t *>(row)[ka0 + lane] = static_cast<uint16_t>(e >> 8);
+                else
+                    reinterpret_cast<uint32_t *>(row)[ka0 + lane] = e + 0x3F800000u;
+            }
+            __syncthreads();
+        }
+    }
 }
 
 // ------------------------------------------------------------------ instantiated tiles -----
@@ -2509,14 +2715,17 @@ static_assert(tab_cands_listed(kTabCands, 7, 7) && tab_cands_listed(kWideCands, 
               "a tile candidate is missing from AMSIM_FOR_TAB_TILES");
 
 // Per operation (defined in amsim_tab.hip, one instantiation per operation and row-length class: WIDE 0
-// rows of 128 entries, 1 longer ones): raise the dynamic LDS limit of every instantiated tile's
-// kernel and check that none uses static LDS; launch the kernel of tile t with rows of 2^rl entries
-// and variant var (kTabNative and kTabApproxSelf: rl = 7).  Both return the first HIP error, and the
-// launch hipErrorInvalidConfiguration for a tile that is not instantiated.
+// rows of 128 entries, 1 longer ones): raise the dynamic LDS limit of every instantiated
+// kernel and check that none uses static LDS; launch the table kernel of tile t with rows of 2^rl entries
+// and variant var (kTabNative and kTabApproxSelf: rl = 7); launch own_kernel of nw waves and class cls on
+// `blocks` workgroups (own_grid).  All return the first HIP error, and the launches
+// hipErrorInvalidConfiguration for a kernel that is not instantiated.
 template <int OP, int WIDE>
 hipError_t tab_attributes_of();
 template <int OP, int WIDE>
-hipError_t tab_launch_of(const Tile &t, int rl, int var, const TabArgs &a, dim3 tiles, hipStream_t st);
+hipError_t tab_launch_of(const Tile &t, int rl, int var, const TabArgs &a, dim3 grid, hipStream_t st);
+template <int OP, int WIDE>
+hipError_t own_launch_of(int nw, int cls, unsigned blocks, const TabArgs &a, const OwnPrep &p, hipStream_t st);
 
 template <int OP>
 hipError_t tab_attributes()
@@ -2525,9 +2734,14 @@ hipError_t tab_attributes()
     return e != hipSuccess ? e : w;
 }
 template <int OP>
-hipError_t tab_launch(const Tile &t, int rl, int var, const TabArgs &a, dim3 tiles, hipStream_t st)
+hipError_t tab_launch(const Tile &t, int rl, int var, const TabArgs &a, dim3 grid, hipStream_t st)
 {
-    return rl == 7 ? tab_launch_of<OP, 0>(t, rl, var, a, tiles, st) : tab_launch_of<OP, 1>(t, rl, var, a, tiles, st);
+    return rl == 7 ? tab_launch_of<OP, 0>(t, rl, var, a, grid, st) : tab_launch_of<OP, 1>(t, rl, var, a, grid, st);
+}
+template <int OP>
+hipError_t own_launch(int nw, int cls, unsigned blocks, const TabArgs &a, const OwnPrep &p, hipStream_t st)
+{
+    return cls == kOwnWide ? own_launch_of<OP, 1>(nw, cls, blocks, a, p, st) : own_launch_of<OP, 0>(nw, cls, blocks, a, p, st);
 }
 
 }  // namespace amsim_detail

@@ -52,34 +52,51 @@ hipError_t tab_attributes_of()
     hipError_t err = hipSuccess;
 #define X(TM, TN, WR, NW, RL)                                                                              \
     if constexpr ((RL > 7) == (WIDE != 0))                                                                  \
-        allow_lds(tab_kernel<OP, TM, TN, WR, NW, RL, kTabApprox>, tab_lds_bytes(TN, WR, NW, RL), err);          \
+        allow_lds(tab_kernel<OP, TM, TN, WR, NW, RL, kTabApprox>, tab_lds_bytes(TN, WR, NW, RL), err);      \
     if constexpr (RL == 7 && WIDE == 0) {                                                                   \
         allow_lds(tab_kernel<OP, TM, TN, WR, NW, 7, kTabNative>, tab_native_lds_bytes(TN, WR, NW), err);    \
         allow_lds(tab_kernel<OP, TM, TN, WR, NW, 7, kTabApproxSelf>, tab_lds_bytes(TN, WR, NW, 7), err);    \
     }
     AMSIM_FOR_TAB_TILES(X)
 #undef X
+    if constexpr (WIDE != 0) {
+        allow_lds(own_kernel<OP, 8, kOwnWide>, own_lds_bytes(8, kOwnWide), err);
+        allow_lds(own_kernel<OP, 4, kOwnWide>, own_lds_bytes(4, kOwnWide), err);
+    } else {
+        allow_lds(own_kernel<OP, 8, kOwnTab>, own_lds_bytes(8, kOwnTab), err);
+        allow_lds(own_kernel<OP, 4, kOwnTab>, own_lds_bytes(4, kOwnTab), err);
+        allow_lds(own_kernel<OP, 8, kOwnNative>, own_lds_bytes(8, kOwnNative), err);
+        allow_lds(own_kernel<OP, 4, kOwnNative>, own_lds_bytes(4, kOwnNative), err);
+    }
     return err;
 }
 
 template <int OP, int WIDE>
-hipError_t tab_launch_of(const Tile &t, int rl, int var, const TabArgs &args, dim3 tiles, hipStream_t st)
+hipError_t own_launch_of(int nw, int cls, unsigned blocks, const TabArgs &a, const OwnPrep &p, hipStream_t st)
 {
-    TabArgs a = args;
-    a.gx = int(tiles.x);
-    a.gy = int(tiles.y);
-    a.gz = int(tiles.z);
-    // the bodies of additive and exact-product tables and the native multiply's matrix-core body tile the result their own way: workgroups for
-    // whichever tiles are more
-    int64_t blocks = int64_t(tiles.x) * tiles.y * tiles.z;
-    if (var == kTabApprox || (var == kTabNative && a.eb != nullptr)) {
-        const int rows = 32 * t.nw, cols = own_cols(a.own_c);
-        const int64_t own = (int64_t(a.R) + rows - 1) / rows * ((int64_t(a.N) + cols - 1) / cols) *
-                            (int64_t(tiles.z) / a.splits * a.own_splits);
-        if (own > blocks) blocks = (own + 7) / 8 * 8;  // a multiple of 8 keeps the XCD order
-    }
-    if (blocks * 64 * t.nw >= int64_t(1) << 32) return hipErrorInvalidConfiguration;
-    const dim3 grid{unsigned(blocks)};
+    bool launched = false;
+    auto run = [&](auto nw_c, auto cls_c) {
+        constexpr int NW = decltype(nw_c)::value, CLS = decltype(cls_c)::value;
+        if constexpr ((CLS == kOwnWide) == (WIDE != 0)) {
+            if (nw == NW && cls == CLS) {
+                hipLaunchKernelGGL((own_kernel<OP, NW, CLS>), dim3(blocks), dim3(64 * NW), own_lds_bytes(NW, CLS), st, a, p);
+                launched = true;
+            }
+        }
+    };
+    auto both = [&](auto cls_c) {
+        run(std::integral_constant<int, 8>{}, cls_c);
+        run(std::integral_constant<int, 4>{}, cls_c);
+    };
+    both(std::integral_constant<int, kOwnTab>{});
+    both(std::integral_constant<int, kOwnWide>{});
+    both(std::integral_constant<int, kOwnNative>{});
+    return launched ? hipGetLastError() : hipErrorInvalidConfiguration;
+}
+
+template <int OP, int WIDE>
+hipError_t tab_launch_of(const Tile &t, int rl, int var, const TabArgs &a, dim3 grid, hipStream_t st)
+{
     bool launched = false;
     auto run = [&](auto tm, auto tn, auto wr, auto nw, auto rl_c) {
         constexpr int TM = decltype(tm)::value, TN = decltype(tn)::value, WR = decltype(wr)::value;
@@ -110,5 +127,7 @@ hipError_t tab_launch_of(const Tile &t, int rl, int var, const TabArgs &args, di
 
 template hipError_t tab_attributes_of<AMSIM_TAB_OP, AMSIM_TAB_WIDE>();
 template hipError_t tab_launch_of<AMSIM_TAB_OP, AMSIM_TAB_WIDE>(const Tile &, int, int, const TabArgs &, dim3, hipStream_t);
+template hipError_t own_launch_of<AMSIM_TAB_OP, AMSIM_TAB_WIDE>(int, int, unsigned, const TabArgs &, const OwnPrep &,
+                                                                hipStream_t);
 
 }  // namespace amsim_detail

@@ -13,6 +13,7 @@
 //     the extremes, with no wrap of the 32-bit forms;
 //   * second-operand element offsets inside the decoded operand, result offsets inside the
 //     result (or the split partial sums).
+//   * the table kernels' LDS: no more than what their own bodies use.
 // Signed overflow anywhere in that arithmetic is reported by the undefined-behaviour sanitizer.
 // Usage: plan_bounds_harness <gemm cases> <conv cases> <seed>.  Prints "OK ..." and exits 0, or
 // prints the first failing case and exits 1.
@@ -316,6 +317,21 @@ void check_conv_pass(Rng &rng, const amsim_conv2d &d, int pass, int mb)
     }
 }
 
+// The table kernels' LDS, which bounds the workgroups on a CU: two slabs of the native multiply's second
+// operand; for the smallest 128-entry tiles the pair path's or exact path's 32 KiB, five workgroups a CU.
+void check_lds()
+{
+    std::snprintf(g_case, sizeof g_case, "LDS");
+#define X(TM, TN, WR, NW, RL)                                                                                       \
+    if (RL == 7)                                                                                                    \
+        expect(tab_native_lds_bytes(TN, WR, NW) == size_t(2) * 16 * TN * (NW / WR) * 4, "native LDS",               \
+               int64_t(tab_native_lds_bytes(TN, WR, NW)), TN);                                                      \
+    if (RL == 7 && NW == 4 && WR == 4)                                                                              \
+        expect(tab_lds_bytes(TN, WR, NW, RL) <= 32768, "4-wave LDS", int64_t(tab_lds_bytes(TN, WR, NW, RL)), TN);
+    AMSIM_FOR_TAB_TILES(X)
+#undef X
+}
+
 amsim_conv2d random_desc(Rng &rng)
 {
     amsim_conv2d d{};
@@ -355,6 +371,7 @@ int main(int argc, char **argv)
     const long n_gemm = argc > 1 ? std::atol(argv[1]) : 10000;
     const long n_conv = argc > 2 ? std::atol(argv[2]) : 10000;
     Rng rng{argc > 3 ? uint64_t(std::atoll(argv[3])) * 0x9E3779B97F4A7C15ull + 1 : 0x1234567ull};
+    check_lds();
     long gemm_done = 0, conv_done = 0, conv_tried = 0;
     const int mbs[] = {7, 7, 7, 1, 4, 8, 9, 10, 11};
     while (gemm_done < n_gemm) {
