@@ -1525,7 +1525,7 @@ PrepJobs prep_jobs(const Mode &md, const uint32_t *lut, int mb, char *ws, const 
     j.fa = fmt_first(md, mb);
     j.fb = fmt_second(md, p, mb);
     j.t.flags = reinterpret_cast<int *>(ws + p.off_eb);
-    if (md.native && small_call(macs, 7)) return j;  // decides nothing on the device
+    if (md.native && (small_call(macs, 7) || p.own_kinds == 0)) return j;  // decides nothing on the device
     j.stats_a = stats_a(ws, p);
     j.stats_b = stats_b(ws, p);
     if (md.native) return j;
@@ -1537,7 +1537,7 @@ PrepJobs prep_jobs(const Mode &md, const uint32_t *lut, int mb, char *ws, const 
     j.t.hl_rows = reinterpret_cast<uint32_t *>(ws + p.off_hl_rows);
     if (p.rl == 7) {
         j.n_tab = table_jobs(mb);
-        j.t.kinds = small_call(macs, p.rl) || narrow_of(md) ? 0 : 1;  // no body for their kinds
+        j.t.kinds = small_call(macs, p.rl) || narrow_of(md) || p.own_kinds == 0 ? 0 : 1;  // no body for their kinds
     } else {
         j.wide = 1;
         j.t.part = reinterpret_cast<uint32_t *>(ws + p.off_wpart);
@@ -1593,7 +1593,11 @@ void set_stats(TabArgs &a, const PrepJobs &j, const Mode &md)
     a.n_a = j.n_a;
     a.n_b = j.n_b;
     a.narrow = narrow_of(md);
-    if (a.narrow && !j.wide) a.own_c = 0;  // no body for them on rows of 128 entries
+    if (a.narrow) {  // only in rounded form, and on rows of 128 entries in none
+        const int rounded = j.wide ? a.own_kinds & (kRunsAddRounded | kRunsExactRounded) : 0;
+        a.own_kinds = rounded | rounded >> 2;
+        if (a.own_kinds == 0) a.own_c = 0;
+    }
     if (j.stats_a == nullptr) a.eb = nullptr;  // a native multiply that decides nothing: no flags
 }
 

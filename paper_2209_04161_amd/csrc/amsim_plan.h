@@ -161,6 +161,8 @@ struct Plan {
     int chunks_per_split;   // 8-step reduction chunks per split
     int64_t own_rows, own_n, own_phases, own_q;  // bodies with tiles of their own: the result and its chunks,
     int own_c, own_splits, own_cps;  // tile width code (own_cols), splits and chunks per split of those bodies (plan_own_tiles)
+    int own_kinds;                   // what runs there (own_kinds; 0: nothing)
+    int own_native;                  // the same for the native multiply
     int64_t out_elems;      // elements of the result (partial sums hold splits of them)
     int Hp, Wp, OHp, OWp, pad_oh, pad_ow;
     bool unfold_w;          // forward / backward-data pass over x unfolded along w
@@ -232,6 +234,57 @@ inline void plan_own_tiles(Plan &p, int64_t rows, int64_t cols, int64_t phases, 
     }
 }
 
+// The kinds of table and forms (kRunsAdd ...) that run in the bodies with tiles of their own, for a result
+// of `cols` columns, which the gathers pad to `gcols`.  Those tiles compute 32 to 128 columns whatever the
+// result has, so narrow results are the gathers': below these counts the gathers were faster, MI355X, at
+// 2^27 to 2^29 products (gathers against bodies, us).  `few`: a pass with at most 9 kernel positions and
+// one stride phase, where a tile reads few records per product.
+//   Rows of 128 entries: additive 3x3 64 -> 16 channels 106 / 122, -> 20 102 / 84; exact 5x5 16 -> 8 129 /
+//     159, -> 9 176 / 77, but 3x3 64 -> 4 78 / 71; native 3x3 64 -> 16 112 / 133, -> 20 139 / 89, GEMM 16384 x
+//     13 x 1152 92 / 79.  GEMMs of 9 to 12 columns that the gathers pad to 16: additive 108 / 86, native 95 / 90.
+//   Wide rows: additive 3x3 64 -> 12 154 / 166 (M = 8), -> 13 172 / 167; rounded -> 24 253 / 272, -> 32
+//     292 / 265 (5x5 16 -> 28 378 / 430); exact -> 4 126 / 145, -> 6 157 / 154; rounded -> 16 269 / 296, -> 20 324 / 282.
+//   Backward weight, whose gathers wait on short rows: 5 columns and up (additive 3x3 32 -> 4 56 / 73, -> 6
+//     80 / 71), wide ones any (-> 2 214 / 193), rounded 9 (additive -> 8 251 / 369, -> 9 588 / 382; exact -> 4 285 /
+//     361, -> 6 404 / 361).
+enum { kPassGemm = 0, kPassConv = 1, kPassWeight = 2 };
+inline int own_kinds(int pass, int64_t cols, int64_t gcols, bool few, bool wide)
+{
+    int k = 0;
+    if (pass == kPassWeight) {
+        if (wide || cols >= 5) k |= kRunsAdd;
+        k |= kRunsExact;
+        if (wide && cols >= 9) k |= kRunsAddRounded;
+        if (wide && cols >= 6) k |= kRunsExactRounded;
+        return k;
+    }
+    if (wide) {
+        if (cols >= 13) k |= kRunsAdd;
+        if (pass == kPassGemm || cols >= (few ? 6 : 9)) k |= kRunsExact;
+        if (cols >= 29) k |= kRunsAddRounded;
+        if (cols >= 20) k |= kRunsExactRounded;
+        return k;
+    }
+    if (cols >= 17 || (pass == kPassGemm && cols >= 9 && cols <= 12 && gcols >= 16)) k |= kRunsAdd;
+    if (pass == kPassGemm || cols >= 9 || few) k |= kRunsExact;
+    return k;
+}
+
+// The same for the native multiply.
+inline int own_native(int pass, int64_t cols, int64_t gcols)
+{
+    const bool runs = pass == kPassWeight ? cols >= 5
+                      : pass == kPassConv ? cols >= 17
+                                          : cols >= 13 || (cols >= 9 && gcols >= 16);
+    return runs ? kRunsExact : 0;
+}
+
+inline void plan_own_kinds(Plan &p, int pass, int64_t cols, bool few)
+{
+    p.own_kinds = own_kinds(pass, cols, p.b_ld, few, p.rl > 7);
+    p.own_native = own_native(pass, cols, p.b_ld);
+}
+
 inline bool valid_m(int m_bits) { return m_bits >= 1 && m_bits <= 11; }
 
 // Transposed rows (the widest entry width, plus the zero row for 128-entry rows), bf16-path rows,
@@ -274,6 +327,7 @@ inline Plan plan_gemm(int64_t m, int64_t n, int64_t k, int m_bits)
     o += align_up(size_t(k) * p.b_ld * 4);
     p.out_elems = m * n;
     plan_own_tiles(p, m, n, 1, ceil_div(k, p.chunk), p.rl > 7, p.splits);
+    plan_own_kinds(p, kPassGemm, n, false);
     p.off_part = o;
     if (p.splits > 1) o += align_up(size_t(p.splits) * m * n * 4);
     p.total = o;
@@ -430,11 +484,15 @@ inline bool bwd_data_unfolds(const amsim_conv2d *d)
     return check_conv(&v, AMSIM_CONV_BWD_DATA) == AMSIM_OK && int64_t(v.n) * v.h * v.w * v.c_in < (int64_t(1) << 29);
 }
 
+// Partial results that the workspace of a plan holds.
+inline int64_t plan_parts(const Plan &p) { return p.own_kinds != 0 ? std::max(p.splits, p.own_splits) : p.splits; }
+
 // The native multiply's matrix-core body has the wide tables' tile widths, in the same workspace.
 inline void plan_native_tiles(Plan &p)
 {
-    const int64_t most = std::max(p.splits, p.own_splits);
+    const int64_t most = plan_parts(p);
     plan_own_tiles(p, p.own_rows, p.own_n, p.own_phases, p.own_q, true, most);
+    p.own_kinds = p.own_native;
 }
 
 // Room for partial sums of the bodies with tiles of their own: up to 64 MiB, or what the gathers' splits take.
@@ -476,6 +534,7 @@ inline Plan plan_conv(const amsim_conv2d *d, int pass, int m_bits)
         p.out_elems = npix_out * s.co;
         plan_own_tiles(p, npix_out, s.co, 1, int64_t(v.kh) * v.kw * p.csplit * ceil_div(v.ci / p.csplit, p.chunk), p.rl > 7,
                        own_most(p));
+        plan_own_kinds(p, kPassConv, s.co, s.kh * s.kw <= 9);
         p.off_a = o;
         o += align_up(size_t(p.a_elems) * 4);
         p.off_b = o;  // decoded w [kh*kw*ci][COp] (unfolded: [kh][cu][COp])
@@ -499,6 +558,7 @@ inline Plan plan_conv(const amsim_conv2d *d, int pass, int m_bits)
         plan_own_tiles(p, rows, s.ci, int64_t(s.sh) * s.sw,
                        ceil_div(s.kh, s.sh) * ceil_div(s.kw, s.sw) * p.csplit * ceil_div(s.co / p.csplit, p.chunk),
                        p.rl > 7, p.splits);
+        plan_own_kinds(p, kPassConv, s.ci, s.kh * s.kw <= 9 && s.sh * s.sw == 1);
         p.off_a = o;
         o += align_up(size_t(p.a_elems) * 4);
         p.off_b = o;  // decoded w^T [kh][kw][co][CIp]
@@ -514,14 +574,14 @@ inline Plan plan_conv(const amsim_conv2d *d, int pass, int m_bits)
         p.a_elems = int64_t(s.n) * p.Hp * p.Wp * s.ci * 3;
         p.out_elems = R * s.co;
         plan_own_tiles(p, R, s.co, 1, int64_t(s.n) * s.oh * ceil_div(s.ow, p.chunk), p.rl > 7, own_most(p));
+        plan_own_kinds(p, kPassWeight, s.co, false);
         p.off_a = o;  // zero-bordered x as step-pair records, one per element
         o += align_up(size_t(p.a_elems) * 4);
         p.off_b = o;  // decoded dy [n*oh*ow][COp]
         o += align_up(size_t(npix_out) * p.b_ld * 4);
     }
     p.off_part = o;
-    const int parts = pass == AMSIM_CONV_BWD_DATA ? p.splits : std::max(p.splits, p.own_splits);
-    if (p.splits > 1) o += align_up(size_t(parts) * p.out_elems * 4);
+    if (p.splits > 1) o += align_up(size_t(plan_parts(p)) * p.out_elems * 4);
     p.total = o;
     return p;
 }
@@ -695,7 +755,8 @@ inline TabArgs tab_geom(const Plan &p, int64_t a_elems, int R, int N)
     a.chunk = p.chunk;
     a.chunks_per_split = p.chunks_per_split;
     a.phases = int(p.own_phases);
-    a.own_c = p.own_c;
+    a.own_c = p.own_kinds != 0 ? p.own_c : 0;
+    a.own_kinds = p.own_kinds;
     a.own_splits = p.own_splits;
     a.own_cps = p.own_cps;
     a.out_elems = p.out_elems;

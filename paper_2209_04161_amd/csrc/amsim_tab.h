@@ -79,6 +79,7 @@ struct TabArgs {
     int phases;            // stride phases (backward data; else 1)
     int own_c;             // bodies with tiles of their own: tile width (own_cols; 0: the call has none),
     int own_splits, own_cps;  // splits and chunks per split
+    int own_kinds;            // and the kinds and forms that run there (kRunsAdd ...)
     int64_t out_elems;   // elements of one split's partial result (splits > 1)
     int Mp, K;           // GEMM
     ConvShape s;
@@ -117,6 +118,9 @@ __device__ __forceinline__ void tab_tile_id(int splits, int &tx, int &ty, int &t
 // Columns of the tiles of a body with tiles of its own (own_kernel), of width code c: the matrix-core
 // bodies' WC (4 or 2), the arithmetic and native bodies' TN (8 or 4).
 __host__ __device__ constexpr int own_cols(int c) { return 16 * c; }
+// TabArgs::own_kinds: the kinds of table that such a body computes in this call, additive and exact
+// product (the latter stands for the native multiply too), and whether in their rounded form as well.
+constexpr int kRunsAdd = 1, kRunsExact = 2, kRunsAddRounded = 4, kRunsExactRounded = 8;
 
 // Workgroup id of `grid` -> tile lid of `tiles`: contiguous ranges of tiles per XCD where the grid is a
 // multiple of 8 (own_grid).  False for a workgroup past the last tile.
@@ -2480,9 +2484,10 @@ constexpr size_t tab_lds_bytes(int tn, int wr, int nw, int rl)
 //
 // CLS: kOwnTab (M <= 7), kOwnWide (M = 8..11) or kOwnNative.
 //   kOwnTab: the kinds of table that the pre-pass's n_tab table workgroups rule out are in
-//     flags[kMissFlag ...]; where both are, only workgroup 0 goes on, to decide between the gathers' paths.
+//     flags[kMissFlag ...]; where both are, or the other does not run here (own_kinds), only workgroup 0
+//     goes on, to decide between the gathers' paths.
 //   kOwnWide: the nparts words of lut_low_bits_body give the entry width and the kind.  A table of no
-//     kind is transposed by the other workgroups:
+//     kind, or whose kind or form does not run here (own_kinds), is transposed by the other workgroups:
 //     row kb (2^m entries of eb bytes) holds entry (ka, kb) at byte ka * eb, through 64 x 64 LDS tiles
 //     (loads along kb, stores along ka).
 //   kOwnNative: the matrix cores' window.
@@ -2551,14 +2556,16 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(4, 4)))
         eb = (lb & 0xFFFFu) == 0u ? 1 : ((lb & 0xFFu) == 0u ? 2 : 4);
     }
     // the native multiply's matrix cores need the exact product's window
-    const int kind = a.own_c == 0 ? 0
-                     : CLS == kOwnNative ? kMmaExact
-                     : (lb & kMissAdd) == 0u ? kMmaAdd
-                     : (lb & kMissExact) == 0u ? kMmaExact : 0;
+    int kind = CLS == kOwnNative ? kMmaExact
+               : (lb & kMissAdd) == 0u ? kMmaAdd
+               : (lb & kMissExact) == 0u ? kMmaExact : 0;
+    const int runs = kind == 0 ? 0 : a.own_kinds >> (kind - 1);  // kRunsAdd, kRunsAddRounded: this kind's bits
+    if ((runs & kRunsAdd) == 0) kind = 0;
+    const bool sure = CLS == kOwnWide && (runs & kRunsAddRounded) != 0;  // computed whatever the operands
     uint32_t id;
     const bool tiled = own_tile_id(blockIdx.x, gridDim.x, own_tiles(a, NW), id);
     int path = 0;
-    if (lead || (kind != 0 && tiled)) {  // uniform over the workgroup
+    if (lead || (kind != 0 && (tiled || !sure))) {  // uniform over the workgroup
         if (!few) fold();
         alo = wave_min(alo);
         ahs = wave_max(ahs);
@@ -2581,6 +2588,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(4, 4)))
         int rounded;
         decide_paths(eb, kind, CLS == kOwnWide, alo, ahs, blo, bhs, true, a.narrow, path, rounded);
         if (CLS == kOwnNative) path = path == 2 + kMmaExact ? 3 : 0;
+        if (path >= 5 && !sure) path = 0;
         path = __builtin_amdgcn_readfirstlane(path);
         if (lead && threadIdx.x == 0) {
             p.flags[1] = path;
@@ -2620,7 +2628,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(4, 4)))
         return;
     }
     if constexpr (CLS == kOwnWide) {
-        if (kind != 0 || lead) return;  // no row is read; workgroup 0 has decided in the meantime
+        if (sure || lead) return;  // no row is read; workgroup 0 has decided in the meantime
         uint32_t(*tile)[kRowTile + 1] = reinterpret_cast<uint32_t(*)[kRowTile + 1]>(smem);
         const int n = 1 << a.m, tiles_1d = n / kRowTile, tiles = tiles_1d * tiles_1d, step = int(gridDim.x) - 1;
         // a sum-indexed table's entries are read at kb = 0 and at ka = 2^m - 1 only

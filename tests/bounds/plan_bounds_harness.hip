@@ -13,6 +13,10 @@
 //     the extremes, with no wrap of the 32-bit forms;
 //   * second-operand element offsets inside the decoded operand, result offsets inside the
 //     result (or the split partial sums).
+//   * the bodies with tiles of their own (own_kernel), of the call's table and of the native multiply:
+//     their splits cover the reduction and none is empty, their partial sums stay in the workspace (which
+//     holds no more than the gathers' where the bodies run nothing), their grid is within the launch limit,
+//     and every tile has exactly one workgroup;
 //   * the table kernels' LDS: no more than what their own bodies use.
 // Signed overflow anywhere in that arithmetic is reported by the undefined-behaviour sanitizer.
 // Usage: plan_bounds_harness <gemm cases> <conv cases> <seed>.  Prints "OK ..." and exits 0, or
@@ -20,6 +24,7 @@
 #include <cinttypes>
 #include <cstdio>
 #include <cstdlib>
+#include <vector>
 
 #include "amsim_plan.h"
 
@@ -77,7 +82,7 @@ void check_table_area(const Plan &p)
     check_region("rows", p.off_rows, rows_bytes(p.rl), p.off_dot_rows);
     check_region("dot rows", p.off_dot_rows, kDotRowsBytes, p.off_hl_rows);
     check_region("hl rows", p.off_hl_rows, p.rl == 7 ? kHlRowsBytes : 0, p.off_eb);
-    check_region("flags", p.off_eb, 3 * sizeof(int), p.off_stats);
+    check_region("flags", p.off_eb, size_t(kMissFlag + 16) * sizeof(int), p.off_stats);
     check_region("stats", p.off_stats, kStatsBytes, p.off_wpart);
     check_region("wide partials", p.off_wpart, p.rl == 7 ? 0 : size_t(kWidePartWords) * 4, p.off_a);
 }
@@ -109,6 +114,66 @@ void check_splits(const TabArgs &a)
     if (OP != OP_BWD_DATA)
         expect(int64_t(a.splits - 1) * a.chunks_per_split < q, "no empty split", int64_t(a.splits - 1) * a.chunks_per_split,
                q);
+    if (a.own_c == 0) return;
+    expect(int64_t(a.own_splits) * a.own_cps >= q, "own splits cover the chunks", int64_t(a.own_splits) * a.own_cps, q);
+    if (OP != OP_BWD_DATA)
+        expect(int64_t(a.own_splits - 1) * a.own_cps < q, "no empty own split", int64_t(a.own_splits - 1) * a.own_cps, q);
+}
+
+long g_own_tilings = 0, g_own_more_splits = 0, g_own_none = 0;
+
+// The bodies with tiles of their own under plan p, whose partial sums end at part_end: a, the call's
+// arguments, and g, the table kernel's grid.
+void check_own_plan(const Plan &p, const TabArgs &a, const TabGrid &g, size_t part_end, int cls)
+{
+    expect(a.phases >= 1 && int64_t(a.phases) * a.splits == int64_t(g.z), "phases x splits", a.phases, g.z);
+    if (p.own_kinds == 0) {
+        ++g_own_none;
+        expect(a.own_c == 0 && own_tiles(a, p.tile.nw) == 0, "no tiles of their own", a.own_c, 0);
+    } else {
+        expect(a.own_c == p.own_c && a.own_c >= 2, "tile width", a.own_c, p.own_c);
+        expect(int64_t(a.own_splits) * a.own_cps >= p.own_q, "own splits cover the reduction", a.own_splits, p.own_q);
+        expect(p.splits > 1 ? a.own_splits >= p.splits : a.own_splits == 1, "splits where the gathers split", a.own_splits,
+               p.splits);
+        if (p.splits > 1)
+            expect(p.off_part + size_t(a.own_splits) * size_t(p.out_elems) * 4 <= part_end, "own partial sums",
+                   int64_t(p.off_part + size_t(a.own_splits) * size_t(p.out_elems) * 4), int64_t(part_end));
+        if (a.own_splits > p.splits) ++g_own_more_splits;
+    }
+    const int nw = p.tile.nw;
+    const int64_t blocks = own_grid(a, nw, cls), tiles = own_tiles(a, nw);
+    expect(own_grid_fits(blocks, nw), "own launch limit", blocks, nw);
+    expect(blocks >= 1 && blocks >= tiles, "a workgroup for every tile", blocks, tiles);
+    if (a.own_c != 0)
+        expect(tiles == ceil_div(a.R, 32 * nw) * ceil_div(a.N, own_cols(a.own_c)) * a.phases * a.own_splits, "own tiles", tiles, 0);
+    if (cls == kOwnWide) expect(blocks >= 2, "workgroups that transpose the table", blocks, 2);
+    if (blocks > 8192) return;
+    std::vector<char> seen(size_t(tiles), 0);
+    int64_t visits = 0;
+    for (int64_t b = 0; b < blocks; ++b) {
+        uint32_t id = 0;
+        if (!own_tile_id(uint32_t(b), uint32_t(blocks), uint32_t(tiles), id)) continue;
+        expect(int64_t(id) < tiles && !seen[id], "a tile visited twice or past the end", id, tiles);
+        seen[id] = 1;
+        ++visits;
+    }
+    expect(visits == tiles, "every tile visited", visits, tiles);
+    ++g_own_tilings;
+}
+
+// The call's table and, where the plan is its plan too (M <= 7), the native multiply.
+template <class Geom>
+void check_own(const Plan &p, const Geom &geom, const TabGrid &g, size_t part_end)
+{
+    if (p.own_kinds == 0)
+        expect(part_end == p.off_part + (p.splits > 1 ? align_up(size_t(p.splits) * size_t(p.out_elems) * 4) : 0),
+               "no room for bodies that run nothing", int64_t(part_end), int64_t(p.off_part));
+    check_own_plan(p, geom(p), g, part_end, p.rl > 7 ? kOwnWide : kOwnTab);
+    if (p.rl == 7) {
+        Plan n = p;
+        plan_native_tiles(n);
+        check_own_plan(n, geom(n), g, part_end, kOwnNative);
+    }
 }
 
 // Offsets of one operation's taps for the tile z (and its phase), sampled rows / taps / steps.
@@ -174,6 +239,12 @@ void check_all_tiles(Rng &rng, const TabArgs &a0, const TabGrid &g, int64_t b_ro
     }
 }
 
+TabArgs with_m(TabArgs a, int mb)
+{
+    a.m = mb;
+    return a;
+}
+
 void check_gemm(Rng &rng, int64_t m, int64_t n, int64_t k, int mb)
 {
     std::snprintf(g_case, sizeof g_case, "gemm m=%" PRId64 " n=%" PRId64 " k=%" PRId64 " M=%d", m, n, k, mb);
@@ -190,6 +261,7 @@ void check_gemm(Rng &rng, int64_t m, int64_t n, int64_t k, int mb)
     const TabGrid g = gemm_grid(p);
     expect(int64_t(g.x) * 64 * p.tile.wr * p.tile.tm == p.a_ld, "row tiles", g.x, p.a_ld);
     expect(p.a_ld >= m && p.b_ld >= n, "padded dims", p.a_ld, p.b_ld);
+    check_own(p, [&](const Plan &pl) { return with_m(gemm_geom(pl, m, n, k, n), mb); }, g, p.total);
     check_all_tiles<OP_GEMM>(rng, a, g, k, p.splits > 1 ? m * n : (m - 1) * n + n, n);
 }
 
@@ -280,6 +352,7 @@ void check_conv_pass(Rng &rng, const amsim_conv2d &d, int pass, int mb)
         expect(v.ci % p.csplit == 0, "channel chunks divide ci", v.ci, p.csplit);
         const TabGrid g = fwd_grid(p, s0);
         expect(int64_t(g.x) * 64 * p.tile.wr * p.tile.tm >= int64_t(s0.n) * s0.oh * s0.ow, "row tiles", g.x, 0);
+        check_own(p, [&](const Plan &pl) { return with_m(fwd_geom(pl, s0), mb); }, g, p.total);
         check_all_tiles<OP_FWD>(rng, a, g, b_rows, p.out_elems, 0);
     } else if (pass == AMSIM_CONV_BWD_DATA) {
         const ConvShape s = p.unfold_w ? shape_of(&(const amsim_conv2d &)unfolded_desc(&d)) : s0;
@@ -304,6 +377,7 @@ void check_conv_pass(Rng &rng, const amsim_conv2d &d, int pass, int mb)
         expect(int64_t(a.a_bytes) == p.a_elems * 4, "a_bytes fits 32 bits", p.a_elems * 4, a.a_bytes);
         expect(s.co % p.csplit == 0, "channel chunks divide co", s.co, p.csplit);
         const TabGrid g = bwd_data_grid(p, s);
+        check_own(p, [&](const Plan &pl) { return with_m(bwd_data_geom(pl, s), mb); }, g, part_end);
         check_all_tiles<OP_BWD_DATA>(rng, a, g, b_rows, p.out_elems, 0);
     } else {
         check_region("bwd_weight x records", p.off_a, size_t(p.a_elems) * 4, p.off_b);
@@ -313,6 +387,7 @@ void check_conv_pass(Rng &rng, const amsim_conv2d &d, int pass, int mb)
         const TabArgs a = bwd_weight_geom(p, s0);
         expect(int64_t(a.a_bytes) == p.a_elems * 4, "a_bytes fits 32 bits", p.a_elems * 4, a.a_bytes);
         const TabGrid g = bwd_weight_grid(p, s0);
+        check_own(p, [&](const Plan &pl) { return with_m(bwd_weight_geom(pl, s0), mb); }, g, p.total);
         check_all_tiles<OP_BWD_WEIGHT>(rng, a, g, b_rows, p.out_elems, 0);
     }
 }
@@ -330,6 +405,40 @@ void check_lds()
         expect(tab_lds_bytes(TN, WR, NW, RL) <= 32768, "4-wave LDS", int64_t(tab_lds_bytes(TN, WR, NW, RL)), TN);
     AMSIM_FOR_TAB_TILES(X)
 #undef X
+}
+
+// Narrow results are the gathers': a body with tiles of its own computes 32 columns or more whatever the
+// result has.  The sides of each line.
+void check_kinds()
+{
+    std::snprintf(g_case, sizeof g_case, "kinds by columns");
+    struct Line {
+        int pass, wide, few, kind, first;  // the first number of columns at which `kind` runs
+    };
+    const Line lines[] = {{kPassConv, 0, 1, kRunsAdd, 17},      {kPassConv, 0, 0, kRunsExact, 9},
+                          {kPassConv, 0, 1, kRunsExact, 1},     {kPassGemm, 0, 0, kRunsExact, 1},
+                          {kPassWeight, 0, 0, kRunsAdd, 5},     {kPassWeight, 0, 0, kRunsExact, 1},
+                          {kPassConv, 1, 1, kRunsAdd, 13},      {kPassGemm, 1, 0, kRunsAdd, 13},
+                          {kPassConv, 1, 1, kRunsExact, 6},     {kPassConv, 1, 0, kRunsExact, 9},
+                          {kPassConv, 1, 1, kRunsAddRounded, 29}, {kPassGemm, 1, 0, kRunsExactRounded, 20},
+                          {kPassWeight, 1, 0, kRunsAddRounded, 9}, {kPassWeight, 1, 0, kRunsExactRounded, 6}};
+    for (const Line &l : lines)
+        for (int c = 1; c <= 64; ++c)
+            expect(((own_kinds(l.pass, c, round_up(c, 4), l.few != 0, l.wide != 0) & l.kind) != 0) == (c >= l.first),
+                   "kind by columns", c, l.first);
+    for (int c = 1; c <= 64; ++c) {
+        expect((own_native(kPassConv, c, round_up(c, 4)) != 0) == (c >= 17), "native convolution by columns", c, 17);
+        expect((own_native(kPassWeight, c, round_up(c, 4)) != 0) == (c >= 5), "native backward weight by columns", c, 5);
+        // GEMMs of 9 to 12 columns: where the gathers pad them to 16
+        expect(((own_kinds(kPassGemm, c, 16, false, false) & kRunsAdd) != 0) == ((c >= 9 && c <= 12) || c >= 17),
+               "additive GEMM by columns", c, 17);
+        expect((own_native(kPassGemm, c, round_up(c, 4)) != 0) == (c >= 13), "native GEMM by columns", c, 13);
+        for (int pass : {kPassGemm, kPassConv, kPassWeight})  // a form that runs rounded runs in the window too
+            for (int few : {0, 1}) {
+                const int k = own_kinds(pass, c, round_up(c, 4), few != 0, true);
+                expect((k >> 2 & ~k & 3) == 0, "rounded implies in the window", k, c);
+            }
+    }
 }
 
 amsim_conv2d random_desc(Rng &rng)
@@ -372,6 +481,7 @@ int main(int argc, char **argv)
     const long n_conv = argc > 2 ? std::atol(argv[2]) : 10000;
     Rng rng{argc > 3 ? uint64_t(std::atoll(argv[3])) * 0x9E3779B97F4A7C15ull + 1 : 0x1234567ull};
     check_lds();
+    check_kinds();
     long gemm_done = 0, conv_done = 0, conv_tried = 0;
     const int mbs[] = {7, 7, 7, 1, 4, 8, 9, 10, 11};
     while (gemm_done < n_gemm) {
@@ -404,7 +514,8 @@ int main(int argc, char **argv)
         }
     }
     std::printf("OK gemm_cases=%ld conv_cases=%ld conv_descriptors_drawn=%ld checks=%ld max_a_bytes=%" PRId64
-                " max_record_end=%" PRId64 " bwd_data_as_fwd=%ld\n",
-                gemm_done, conv_done, conv_tried, g_checks, g_max_a_bytes, g_max_offset, g_bwd_as_fwd);
+                " max_record_end=%" PRId64 " bwd_data_as_fwd=%ld own_tilings=%ld own_more_splits=%ld own_none=%ld\n",
+                gemm_done, conv_done, conv_tried, g_checks, g_max_a_bytes, g_max_offset, g_bwd_as_fwd, g_own_tilings,
+                g_own_more_splits, g_own_none);
     return 0;
 }

@@ -45,3 +45,5 @@ def test_plans_and_taps_stay_in_bounds(harness, seed):
     assert int(fields["max_a_bytes"]) > 2 ** 31, line[0]
     # stride-1 backward-data passes that take the forward route are among them
     assert int(fields["bwd_data_as_fwd"]) > 100, line[0]
+    # and tilings of the bodies with tiles of their own, with more splits than the gathers', and calls without
+    assert min(int(fields[k]) for k in ("own_tilings", "own_more_splits", "own_none")) > 100, line[0]
