@@ -264,7 +264,9 @@ def _gemm_ws_bytes(trans_a, trans_b, m, n, k, m_bits) -> int:
 
 
 def amsim_gemm_workspace_size(trans_a, trans_b, m, n, k, m_bits) -> int:
-    return _gemm_ws_bytes(int(trans_a), int(trans_b), m, n, k, int(m_bits))
+    # plain integers alone are cached by value (a tensor would be by its identity, and may change)
+    query = _gemm_ws_bytes if type(m) is type(n) is type(k) is int else _gemm_ws_bytes.__wrapped__
+    return query(int(trans_a), int(trans_b), m, n, k, int(m_bits))
 
 
 def _workspace(nbytes, device):

@@ -204,3 +204,20 @@ def test_product_path_does_not_touch_the_oracle():
                     text = f.read()
                 assert "import oracle" not in text and "from oracle" not in text, fn
                 assert "amsim_oracle" not in text and "orc_" not in text, fn
+
+
+def test_workspace_size_of_sizes_that_are_no_plain_integers(L):
+    """The cached query answers by value: a size held in a tensor that changes, in a numpy array or scalar; a
+    float is refused."""
+    torch = pytest.importorskip("torch")
+    small, large = (binding.amsim_gemm_workspace_size(0, 0, m, 64, 64, 7) for m in (64, 4096))
+    assert small != large
+    size = torch.tensor(64)
+    assert binding.amsim_gemm_workspace_size(0, 0, size, 64, 64, 7) == small
+    size.fill_(4096)
+    assert binding.amsim_gemm_workspace_size(0, 0, size, 64, 64, 7) == large
+    for m in (np.array(4096), np.int64(4096)):
+        assert binding.amsim_gemm_workspace_size(0, 0, m, 64, 64, 7) == large
+    for m in (64.0, np.float64(64)):
+        with pytest.raises(ctypes.ArgumentError):
+            binding.amsim_gemm_workspace_size(0, 0, m, 64, 64, 7)
