@@ -167,7 +167,8 @@ typedef struct amsim_conv2d {
  * input itself) and needs that GEMM's workspace.  A stride-1 backward-data pass with every pad at
  * most the kernel extent minus one and c_out >= 16 runs as the forward pass over dy (padded by the
  * kernel extent minus one minus each pad) with the weights reversed in both kernel axes and c_in,
- * c_out exchanged -- the same products -- and needs that forward pass's workspace. */
+ * c_out exchanged -- the same products -- and needs that forward pass's workspace.  Forward and
+ * backward-weight sizes may hold up to 64 MiB of partial sums for tables that are computed. */
 int amsim_conv2d_workspace_size(const amsim_conv2d *desc, int pass, int m_bits, size_t *bytes);
 
 /* Forward propagation (Algorithm 3): y[n,oh,ow,co] = sum_{kh,kw,ci}
@@ -259,7 +260,9 @@ int approx_mul_ew_ex(const amsim_options *opt, int64_t n, const float *a, const 
  * Measurement support (no paper counterpart; the paper reports per-batch wall time only).
  * Between amsim_profile_start and amsim_profile_stop, every launch of a main kernel -- the
  * GEMM kernel of approx_gemm and the three convolution kernels, not their decode pre-passes
- * -- is bracketed by two HIP events recorded on the stream it is launched on.  The events are
+ * -- is bracketed by two HIP events recorded on the stream it is launched on.  Where a kernel
+ * that computes the table (or transposes a wide table's rows) runs before the table kernel, the
+ * two are one bracket.  The events are
  * timing-only (created without the system-scope fence on completion), so they add no cache
  * writeback around the kernels they time; they order nothing for the host.
  *   amsim_profile_start(max_launches): creates that many event pairs (host-side HIP calls; do

@@ -159,7 +159,7 @@ struct Plan {
     int64_t a_elems;      // conv: elements of the decoded first operand
     int splits;           // reduction splits
     int chunks_per_split;   // 8-step reduction chunks per split
-    int64_t own_rows, own_n, own_phases, own_q;  // bodies with tiles of their own: the result and its chunks,
+    int64_t own_rows, own_n, own_phases, own_q;  // bodies with tiles of their own: the result and its chunks
     int own_c, own_splits, own_cps;  // tile width code (own_cols), splits and chunks per split of those bodies (plan_own_tiles)
     int own_kinds;                   // what runs there (own_kinds; 0: nothing)
     int own_native;                  // the same for the native multiply
@@ -190,9 +190,10 @@ inline void plan_tab_split(Plan &p, int64_t taps, int64_t count)
 // most `most` (the partial sums' room); tiles half as wide where the wider ones are too few.  Priced
 // in slabs of 4 chunks: a workgroup of 8 waves and 64 (wide tables: 128) columns takes ~3 us a slab of
 // its CU's time (44 T products/s over the chip), half as wide a tile ~60% of that, CUs with fewer than
-// 8 waves half as long again, and a split's partial sums are written and read at ~4 TB/s (measured on MI355X with the gathers' splits and wide tiles, then with these: the
-// ResNet-50 stem's backward-weight kernel 347 -> 288 us, a 3x3 128 -> 128 layer's at M = 11 1263 ->
-// 438 us, the GEMM 1024^3 with the exact product in a (1, 5, 10) format 206 -> 118 us).
+// 8 waves half as long again, and a split's partial sums are written and read at ~4 TB/s (measured on
+// MI355X with the gathers' splits and wide tiles, then with these: the ResNet-50 stem's backward-weight
+// kernel 347 -> 288 us, a 3x3 128 -> 128 layer's at M = 11 1263 -> 438 us, the GEMM 1024^3 with the exact
+// product in a (1, 5, 10) format 206 -> 118 us).
 inline void plan_own_tiles(Plan &p, int64_t rows, int64_t cols, int64_t phases, int64_t q, bool wide, int64_t most)
 {
     p.own_rows = rows;

@@ -9,8 +9,8 @@
 // lanes gather from it with their first-operand mantissas.  For 1-byte tables and operands
 // whose exponents keep every product normal, the bf16 pair path folds the second operand into
 // the staged entries and adds two steps' products with one dot instruction.  Tables that are an
-// integer sum of the mantissas, or the exact product, are computed without a table and added on the
-// matrix cores (large calls).
+// integer sum of the mantissas, or the exact product, are computed without a table, and added on the
+// matrix cores (M <= 7, large calls) or in FP32 (M = 8..11), in a kernel of their own (own_kernel).
 #pragma once
 
 #include <type_traits>
@@ -1569,7 +1569,7 @@ __device__ __forceinline__ void tab_body_dot(const TabArgs &a)
 // ------------------------------------------------- matrix-core bodies (M = 3..7)
 // Two kinds of table need no table lookup inside the bf16 path's operand window (decide_paths), and
 // let the matrix cores add the products.  The table preparation checks every entry for both
-// (flags[3]).  The first operand a and the second operand b are bf16 bit patterns here, cut to M
+// (flags[kMissFlag ...]).  The first operand a and the second operand b are bf16 bit patterns here, cut to M
 // mantissa bits.
 //
 // kMmaAdd, an additive table (Mitchell's): entry (ka, kb) = (ka + kb) << (23 - M), the carry falling
@@ -2270,15 +2270,15 @@ __device__ __forceinline__ int exact_needs_rounded_products(bool have_stats, boo
 //     exponent field Ea + Eb - 127 + carry in [1, 254], and v * pb (Eb + carry) stays below 255;
 //   path 2, the hi/lo path (2-byte entries): also the low halves' products normal -- v_lo >=
 //     2^-15 times pb normal as a bf16 (Eb >= 16) and times pa normal (Ea + Eb - 127 - 15 >= 1);
-//   paths 3 and 4 (2 + kind), the matrix-core bodies (kind: the table's, 0 in a small call, whose
-//     launches take longer than its products: the kernel that decides its path itself leaves them out,
-//     which keeps it small -- with them a 64^3 GEMM's took 9.2 us instead of 6.1):
+//   paths 3 and 4 (2 + kind), the matrix-core bodies of own_kernel (kind: the table's, 0 in a call that
+//     does not run it: a small one, whose launches take longer than its products, or a narrow result):
 //   path 3, in path 1's window, Ea + carry below 255 too: an additive table (kind kMmaAdd);
 //   path 4, in path 1's window: the exact product (kind kMmaExact);
 //   path 0, the exact path, whose product form is `rounded`.
 // With wide tables (rows of 256 entries or more) paths 3 and 4 are the arithmetic bodies of the two
 // kinds, 5 and 6 (4 + kind) their rounded form for any other operands, and there is no path 1 or 2.
-// have: the decode passes recorded statistics (not for the native multiply).
+// The native multiply has path 3, its matrix-core body, in the exact product's window, else 0.
+// have: the decode passes recorded statistics.
 __device__ __forceinline__ void decide_paths(int eb, int kind, bool wide, uint32_t a_lo, uint32_t a_hs, uint32_t b_lo, uint32_t b_hs,
                                              bool have, int narrow, int &path, int &rounded)
 {
@@ -2487,9 +2487,9 @@ constexpr size_t tab_lds_bytes(int tn, int wr, int nw, int rl)
 //     flags[kMissFlag ...]; where both are, or the other does not run here (own_kinds), only workgroup 0
 //     goes on, to decide between the gathers' paths.
 //   kOwnWide: the nparts words of lut_low_bits_body give the entry width and the kind.  A table of no
-//     kind, or whose kind or form does not run here (own_kinds), is transposed by the other workgroups:
-//     row kb (2^m entries of eb bytes) holds entry (ka, kb) at byte ka * eb, through 64 x 64 LDS tiles
-//     (loads along kb, stores along ka).
+//     kind, or whose kind or form does not run here (own_kinds), is transposed by the workgroups after
+//     the first: row kb (2^m entries of eb bytes) holds entry (ka, kb) at byte ka * eb, through 64 x 64
+//     LDS tiles (loads along kb, stores along ka).
 //   kOwnNative: the matrix cores' window.
 // Workgroup 0 writes flags[1], the path, and flags[2], the exact path's product form; kOwnWide also
 // flags[0], the entry width, and flags[3], whether the table is sum-indexed.

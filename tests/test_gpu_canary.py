@@ -6,7 +6,8 @@ allocation whose tail holds another pattern.  After the call both guards must be
 the result must equal bit for bit the result of an ordinary call (the library is deterministic).
 The shapes take every route a pass has: direct and split reductions, the forward and the
 stride-phase backward-data kernels, the w-unfolded forward and backward-data passes, pointwise
-passes run as GEMMs, and the wide sum-indexed table.
+passes run as GEMMs, and a wide table that is computed; test_gpu_paths.py guards the large calls'
+bodies and the gathers' on wide tables.
 """
 import numpy as np
 import pytest
@@ -28,7 +29,7 @@ CASES = [
     ("few channels (unfolded passes)", W.conv_desc(2, 12, 13, 3, 6, 5, 5, 1, 2), 7),
     ("long reduction, few outputs (split reductions)", W.conv_desc(8, 30, 30, 4, 4, 3, 3, 1, 1), 7),
     ("pointwise (GEMM route)", W.conv_desc(2, 7, 9, 40, 24, 1, 1), 7),
-    ("wide sum-indexed table", W.conv_desc(2, 9, 9, 32, 24, 3, 3, 1, 1), 11),
+    ("wide additive table", W.conv_desc(2, 9, 9, 32, 24, 3, 3, 1, 1), 11),
 ]
 
 
@@ -88,7 +89,7 @@ GEMM_CASES = [
     ("vector, m = 1", (1, 3000, 700), 7),
     ("vector, n = 1", (3000, 1, 700), 7),
     ("outer product, k = 1", (300, 200, 1), 7),
-    ("wide sum-indexed table", (200, 72, 300), 11),
+    ("wide additive table", (200, 72, 300), 11),
 ]
 
 

@@ -8,6 +8,10 @@ IEEE Inf/NaN handling.  These tests run every such case through multi-step sums 
 slabs), including a product that overflows next to a large opposite-signed partial sum, NaN and
 +-Inf inside sums, sums that overflow, and operands just inside and just outside each window
 threshold, compared element by element with the oracle.
+
+Large calls (2^27 products) and wide tables recognise both models' tables and compute them in bodies of
+their own, with thresholds of their own; test_gpu_paths.py has the general bodies' thresholds there, on
+tables one entry away, and says which body each call takes.
 """
 import numpy as np
 import pytest
@@ -160,6 +164,8 @@ HL_THRESHOLDS = [
 
 @pytest.mark.parametrize("ti", range(len(HL_THRESHOLDS)))
 def test_gemm_window_thresholds_exact_trunc(B, ti):
+    """4096 x 4096 x 16, a large call: this table is computed on either side of these thresholds (its body has
+    the bf16 path's window).  The hi/lo path's decision is in the small calls below."""
     name, ra, rb = HL_THRESHOLDS[ti]
     rng = np.random.default_rng(1100 + ti)
     A = _window_operands(rng, (4096, 16), *ra)
@@ -171,7 +177,7 @@ def test_gemm_window_thresholds_exact_trunc(B, ti):
 
 
 # Calls of fewer than 2^27 products decide their path inside the table kernel; larger calls take it
-# from a flags launch after the pre-pass.  Both decisions, on every threshold and special case,
+# from a launch after the pre-pass.  Both decisions, on every threshold and special case,
 # at both sizes: A is rows x 64, B 64 x cols.
 SIZES = {"small": (300, 96), "large": (4096, 1024)}   # 1.8M and 268M products
 
@@ -248,7 +254,7 @@ def test_conv_passes_exact_path_multi_step(B, special):
 
 @pytest.mark.parametrize("special", ["huge", "naninf"])
 def test_conv_passes_exact_path_large_calls(B, special):
-    """The exact path on calls of more than 2^27 products (path flags from their own launch), each
+    """The exact path on calls of more than 2^27 products (path flags from a launch of their own), each
     pass on seeded sampled outputs: stride 2 and padding 1, 16 x 33 x 31 x 64 -> 64 channels."""
     p = W.conv_desc(16, 33, 31, 64, 64, 3, 3, 2, 1)
     oh, ow = W.conv_out_hw(p)
@@ -395,9 +401,9 @@ def test_conv_border_products_zero_signs(B, ci, model):
 
 @pytest.mark.parametrize("pass_id", [0, 1, 2])
 def test_exact_trunc_conv_passes_on_four_wave_tiles(B, pass_id):
-    """The 2-byte (exact bfloat16-truncation) table on the hi/lo path in 4-wave tiles: the ResNet
-    3x3 shape at batch 8, whose backward-weight pass (576 rows) takes a 4-wave, 8-column tile;
-    seeded sampled outputs against the oracle."""
+    """The 2-byte (exact bfloat16-truncation) table at the ResNet 3x3 shape and batch 8, whose backward-weight
+    pass (576 rows) has a 4-wave, 8-column tile; seeded sampled outputs against the oracle.  This table is
+    computed; test_gpu_paths.py has the hi/lo path on the same passes."""
     p = W.conv_desc(8, 32, 32, 64, 64, 3, 3, 1, 1)
     x, w, dy = W.resnet_conv_inputs(p, seed=1800)
     lut = dev_lut(B, "exact_trunc", 7)

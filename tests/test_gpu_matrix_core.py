@@ -1,5 +1,5 @@
-"""The matrix-core bodies of the table kernels (additive and exact-product tables, M = 3..7) against
-the general bodies and the oracle.
+"""The bodies that compute additive and exact-product tables (matrix cores at M = 3..7, FP32 at M = 8..11)
+and the native multiply's, against the general bodies and the oracle.
 
 A table with one entry changed takes the general path: (2^M - 1, 2^M - 1), which the operands here never
 select, so both paths have the same products.  Shapes sit at the edges of the matrix-core tiles (128 or

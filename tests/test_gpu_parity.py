@@ -307,8 +307,8 @@ GEMM_SHAPES = [(64, 64, 64), (1, 1, 1), (3, 17, 63), (65, 1000, 17), (130, 7, 30
 @pytest.mark.parametrize("shape", GEMM_SHAPES)
 @pytest.mark.parametrize("model,m", [("mitchell", 7), ("mitchell", 11), ("exact_trunc", 11)])
 def test_gemm_matches_oracle(B, shape, model, m):
-    """M = 11: Mitchell's table is sum-indexed (read from one g array), the exact truncated
-    product's is not (rows staged per column and step)."""
+    """M = 11: both models' tables are computed; test_gpu_paths.py has the sum-indexed table's and the
+    staged rows' bodies."""
     M, N, K = shape
     A = W.uniform((M, K), -1, 1, 1000 + M)
     Bm = W.uniform((K, N), -1, 1, 2000 + N)
@@ -561,8 +561,8 @@ def test_resnet_3x3_conv_full_size(B, pass_name):
 
 
 def test_resnet_3x3_conv_full_size_two_byte_table(B):
-    """ResNet 3x3 at full size with the exact-truncation table (2-byte entries): the forward and
-    backward-data passes take the hi/lo path, backward-weight the exact path."""
+    """ResNet 3x3 at full size with the exact-truncation table (2-byte entries), which large calls compute
+    as the exact product on the matrix cores."""
     cfg = W.RESNET_3X3
     _check_conv_full(B, cfg["conv"], cfg["m_bits"], seed=3200, model="exact_trunc", name="resnet 3x3 exact_trunc")
 

@@ -2,7 +2,7 @@
 
 The table preparation checks every entry of a wide table (M = 8..11) for this property, and the
 table kernels then read one array g of 2^(M+1) factors instead of staging a table row per column
-and step; any other table keeps the row staging.  The cases run GEMMs over every mantissa pair of
+and step; any other table keeps the row staging (Mitchell's own and the exact product's are computed).  The cases run GEMMs over every mantissa pair of
 an M = 8 table, built from Mitchell's (which is sum-indexed) with entries changed:
 * a whole anti-diagonal changed alike, once below and once above s = 2^M - 1: still sum-indexed,
   and the changed products must come from the table, not from Mitchell's formula;
