@@ -317,6 +317,16 @@ def test_gemm_matches_oracle(B, shape, model, m):
     assert_within_tolerance(C, ref, S, "gemm %s %s M=%d" % (shape, model, m))
 
 
+@pytest.mark.parametrize("chunks", list(range(2, 18)) + [33])
+def test_gemm_split_counts(B, chunks):
+    """A small GEMM splits its reduction down to 8-step chunks: sums over every remainder of eight splits.
+    A split left out or added twice is far beyond the tolerance."""
+    A, Bm = W.uniform((20, 8 * chunks), 0.5, 1, 3000 + chunks), W.uniform((8 * chunks, 24), 0.5, 1, 3100 + chunks)
+    C = host(B.approx_gemm(cuda(A), cuda(Bm), dev_lut(B, "mitchell", 7), 7))
+    ref, S = oracle.gemm(oracle.MITCHELL, 7, A, Bm)
+    assert_within_tolerance(C, ref, S, "gemm of %d chunks" % chunks)
+
+
 @pytest.mark.parametrize("ta,tb", [(True, False), (False, True), (True, True)])
 @pytest.mark.parametrize("m", [3, 7, 8])
 def test_gemm_transposes(B, ta, tb, m):
