@@ -125,6 +125,9 @@ PATHS = (
     + [("exact_trunc", "general", 7, 8, (4096, 1024, 64), r, p) for r, p in ((HL_IN, 2), (HL_B15, 0), (HL_IN2, 2), (HL_142, 0))]
     + [("mitchell", "kind", 6, 8, LARGE, MID, 3), ("exact_trunc", "kind", 4, 8, LARGE, MID, 4),
        ("mitchell", "kind", 2, 8, LARGE, MID, 1), ("mitchell", "kind", 7, 5, LARGE, ((112, 142), (112, 142)), 0)]
+    # full-size products on the gathers: the benchmark's GEMM, and wide tables from g and from staged rows
+    + [("mitchell", "general", 7, 8, (4096, 4096, 4096), MID, 1), ("exact_trunc", "general", 7, 8, (4096, 4096, 1024), MID, 2),
+       ("mitchell", "sum", 11, 8, (4096, 4096, 512), MID, 0), ("exact_trunc", "general", 11, 8, (4096, 4096, 512), MID, 0)]
     # narrow results are the gathers' (the exact product's GEMMs are not)
     + [("mitchell", "kind", 7, 8, (8192, 16, 1024), MID, 1), ("mitchell", "kind", 7, 8, (8192, 17, 1024), MID, 3),
        ("exact_trunc", "kind", 7, 8, (65536, 2, 1024), MID, 4), ("native", "kind", 7, 8, (16384, 8, 1024), MID, UNSET),
@@ -193,6 +196,7 @@ CONVS = [
     (4, 15, 17, 12, 24, 3, 1, 1, 9, 8, ((1, 1), (0, 1), (1, 1))),
     (4, 15, 17, 20, 30, 3, 2, 1, 10, 5, ((1, 1), (0, 1), (1, 1))),
     (4, 15, 17, 20, 8, 3, 1, 1, 11, 5, ((0, 0), (0, 1), (0, 1))),
+    (128, 32, 32, 64, 64, 3, 1, 1, 7, 8, ((1, 1), (1, 1), (1, 1))),  # the benchmark's ResNet 3x3 layer
 ]
 
 
